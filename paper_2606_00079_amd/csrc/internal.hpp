@@ -51,6 +51,17 @@ class KernelTimer {
   void* start_ = nullptr;
 };
 
+// Tridiagonal reduction of the symmetric fp64 M [n][n] in one cooperative
+// launch (tridiag.hip): the diagonals d [n] and e [n-1], tau [n-1] and the
+// reflectors by rows into V [n][n].  `fits`: whether this device holds an
+// n x n matrix that way; `work` has `bytes` bytes, *err_dev (in it) is
+// nonzero after a run that failed.  False if the launch was refused (nothing
+// was computed).
+bool tridiag_resident_fits(int64_t n);
+size_t tridiag_resident_bytes(int64_t n);
+bool tridiag_resident(const double* M, int64_t n, double* V, double* dvec, double* evec,
+                      double* tau, void* work, int** err_dev, void* stream);
+
 // True when every pointer is 16-byte aligned (the kernels use 16-byte
 // vector accesses on device buffers).
 inline bool aligned16(std::initializer_list<const void*> ptrs) {

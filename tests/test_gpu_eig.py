@@ -64,6 +64,21 @@ def test_separated_spectrum_matches_oracle(n, r):
     _check_invariants(M, Ut, ev, r)
 
 
+@pytest.mark.parametrize("n,r", [(255, 9), (256, 9), (513, 9), (1024, 9), (1025, 9), (1537, 9),
+                                 (2041, 9), (2048, 9), (2049, 9)])
+def test_resident_reduction_edges(n, r):
+    """Sizes at the edges of the in-register reduction: columns per thread,
+    threads per workgroup, a ragged last workgroup, the largest size and the
+    first one past it (the same bars as the smaller sizes: fp64 arithmetic,
+    gaps of 1, an fp32 result)."""
+    say("resident edges", n, r)
+    M = _separated(n, seed=n)
+    Ut, ev, _ = bm.shared_basis_gpu(torch.from_numpy(M).to(DEV), r)
+    Uref, lref = oracle.shared_basis(M, r)
+    assert np.max(np.abs(ev - lref)) <= 1e-11 * n
+    assert np.max(np.abs(Ut.cpu().numpy() - Uref)) <= 2e-6
+
+
 @pytest.mark.parametrize("n,r", [(4133, 200)])
 def test_large_separated_spectrum_matches_oracle(n, r):
     """A larger, ragged size (4133: no panel or tile boundary lines up with
