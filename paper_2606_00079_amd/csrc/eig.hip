@@ -23,13 +23,13 @@
 //                       row);
 //      then trail_kernel applies A_t -= V W^T + W V^T to the trailing block
 //      once per panel.
-//   2. The selected eigenpairs of T on the device: eigenvalues n-r+1..n by
-//      bisection on Sturm counts (bisect_kernel, a thread per eigenvalue),
-//      eigenvectors by inverse iteration with a tridiagonal LU with partial
-//      pivoting (inviter_kernel, a thread per eigenvector, three solves from
-//      a hashed start vector).  Vectors of eigenvalues closer than 1e-7 ||T||
-//      (a cluster) are made orthonormal by modified Gram-Schmidt
-//      (mgs_kernel); others are orthogonal to about eps ||T|| / gap.
+//   2. The selected eigenpairs of T on the device (trieig.hip): multisection
+//      on Sturm counts and twisted factorizations.  Vectors of eigenvalues
+//      closer than 1e-7 ||T|| (a cluster) come from inverse iteration with a
+//      tridiagonal LU with partial pivoting instead (inviter_kernel, a thread
+//      per eigenvector, three solves from a hashed start vector) and are made
+//      orthonormal by modified Gram-Schmidt (mgs_kernel); others are
+//      orthogonal to about eps ||T|| / gap.
 //   3. Back-transformation U = Q Z = H_0 H_1 ... H_{n-2} Z, one panel at a
 //      time from the last, with the compact form H_j0 ... H_{j0+nb-1} =
 //      I - V T V^T (T upper triangular from tau and V V^T).
@@ -40,6 +40,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -398,52 +399,6 @@ __global__ __launch_bounds__(256) void zupdate_kernel(double* __restrict__ Zt, i
   }
 }
 
-// Number of eigenvalues of the tridiagonal (d, e) below x (the negative
-// pivots of the LDL^T factorization of T - x I), pivots kept away from 0.
-__device__ double sturm_below(const double* __restrict__ d, const double* __restrict__ e,
-                              int64_t n, double x, double pivmin, int64_t* count) {
-  double q = d[0] - x;
-  int64_t c = q < 0.0;
-  for (int64_t j = 1; j < n; ++j) {
-    if (fabs(q) < pivmin) q = -pivmin;
-    q = d[j] - x - e[j - 1] * e[j - 1] / q;
-    c += q < 0.0;
-  }
-  *count = c;
-  return q;
-}
-
-// w[k] = eigenvalue t0 + k (0-based, ascending): one wave per eigenvalue
-// splits [lo, hi] at 64 interior points per step (lane l evaluates the
-// Sturm count at lo + (hi - lo)(l + 1)/65); the counts grow with x, so the
-// lanes whose count is <= t form a prefix and the new interval is the gap
-// after it.  Stops when the interval is atol wide or the points no longer
-// fall strictly inside.
-__global__ __launch_bounds__(256) void bisect_kernel(const double* __restrict__ d,
-                                                     const double* __restrict__ e, int64_t n,
-                                                     int64_t r, int64_t t0, double lo0, double hi0,
-                                                     double pivmin, double atol,
-                                                     double* __restrict__ w) {
-  const int lane = threadIdx.x & 63;
-  const int64_t k = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (k >= r) return;  // whole wave
-  const int64_t t = t0 + k;
-  double lo = lo0, hi = hi0;
-  for (int it = 0; it < 64 && hi - lo > atol; ++it) {
-    const double x = lo + (hi - lo) * (static_cast<double>(lane + 1) / 65.0);
-    const bool inside = x > lo && x < hi;
-    if (__ballot(inside) != ~0ull) break;  // the interval is a few ulps wide
-    int64_t cnt;
-    sturm_below(d, e, n, x, pivmin, &cnt);
-    const int p = __popcll(__ballot(cnt <= t));  // lanes 0..p-1 have count <= t
-    const double xl = __shfl(x, p > 0 ? p - 1 : 0, 64);
-    const double xh = __shfl(x, p < 64 ? p : 63, 64);
-    lo = p > 0 ? xl : lo;
-    hi = p < 64 ? xh : hi;
-  }
-  if (lane == 0) w[k] = 0.5 * (lo + hi);
-}
-
 // Start vector entry j of eigenvector k: a counter hash (splitmix64 of the
 // pair) mapped to [-1, 1).
 __device__ __forceinline__ double start_entry(int64_t k, int64_t j) {
@@ -454,7 +409,7 @@ __device__ __forceinline__ double start_entry(int64_t k, int64_t j) {
   return static_cast<double>(z >> 11) * (2.0 / 9007199254740992.0) - 1.0;
 }
 
-// Eigenvector of eigenvalue w[k] by inverse iteration: three solves of
+// Eigenvector of eigenvalue w[list[k]], one of a cluster, by inverse iteration: three solves of
 // (T - w I) x = b, b the previous x scaled to max |x| = 1, with T - w I
 // factored by Gaussian elimination with partial pivoting (U has two
 // superdiagonals; pivots below pivmin in magnitude are set to +-pivmin).
@@ -463,18 +418,18 @@ __device__ __forceinline__ double start_entry(int64_t k, int64_t j) {
 __global__ __launch_bounds__(64) void inviter_kernel(const double* __restrict__ d,
                                                      const double* __restrict__ e, int64_t n,
                                                      int64_t r, const double* __restrict__ w,
-                                                     double pivmin, double* __restrict__ work,
+                                                     const int64_t* __restrict__ list, double pivmin, double* __restrict__ work,
                                                      double* __restrict__ Z) {
   const int64_t k = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x;
   if (k >= r) return;
-  const double lam = w[k];
+  const double lam = w[list[k]];
   double* U0 = work;
   double* U1 = work + n * r;
   double* U2 = work + 2 * n * r;
   double* Y = work + 3 * n * r;
   auto at = [&](int64_t j) { return j * r + k; };
   auto guard = [&](double p) { return fabs(p) >= pivmin ? p : (p < 0.0 ? -pivmin : pivmin); };
-  for (int64_t j = 0; j < n; ++j) Z[at(j)] = start_entry(k, j);
+  for (int64_t j = 0; j < n; ++j) Z[at(j)] = start_entry(list[k], j);
   for (int iter = 0; iter < 3; ++iter) {
     double p0 = d[0] - lam, p1 = n > 1 ? e[0] : 0.0, p2 = 0.0, y = Z[at(0)];
 #pragma unroll 8
@@ -558,9 +513,10 @@ __global__ __launch_bounds__(256) void mgs_kernel(double* __restrict__ Z, int64_
     }
 }
 
-// Zt[k][j] = Z[j][k] (32 x 32 tiles through LDS).
-__global__ __launch_bounds__(256) void transpose_kernel(const double* __restrict__ Z, int64_t n,
-                                                        int64_t r, double* __restrict__ Zt) {
+// Zt[list[k]][j] = Z[j][k], k < r (32 x 32 tiles through LDS).
+__global__ __launch_bounds__(256) void scatter_kernel(const double* __restrict__ Z, int64_t n,
+                                                      int64_t r, const int64_t* __restrict__ list,
+                                                      double* __restrict__ Zt) {
   __shared__ double tile[32][33];
   const int64_t j0 = static_cast<int64_t>(blockIdx.x) * 32, k0 = static_cast<int64_t>(blockIdx.y) * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
@@ -571,7 +527,7 @@ __global__ __launch_bounds__(256) void transpose_kernel(const double* __restrict
   __syncthreads();
   for (int q = ty; q < 32; q += 8) {
     const int64_t k = k0 + q, j = j0 + tx;
-    if (k < r && j < n) Zt[k * n + j] = tile[tx][q];
+    if (k < r && j < n) Zt[list[k] * n + j] = tile[tx][q];
   }
 }
 
@@ -630,16 +586,18 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t 
   bitsmoe_status st;
   // work matrix (M, then the reflectors by rows), Z^T, and small buffers:
   // Wp [NB][n], trsymv output [n + 2 NB], d, e, tau, v [n], G and T [NB][NB],
-  // X [r][NB], eigenvalues [r]
+  // X [r][NB], the in-register reduction's exchange, and what the host reads:
+  // eigenvalues [r], info [8], the reduction's error flag, a flag per vector [r]
   double* A = static_cast<double*>(scratch(kScratchA, static_cast<size_t>(n * n) * 8, stream, &st));
   if (!A) return st;
   double* Zt = static_cast<double*>(scratch(kScratchB, static_cast<size_t>(r * n) * 8, stream, &st));
   if (!Zt) return st;
   const int64_t npan = (n - 1 + NB - 1) / NB;
-  const size_t small = static_cast<size_t>(NB * n + (n + 2 * NB) + 4 * n +
-                                           2 * std::max<int64_t>(npan, 1) * NB * NB + r * NB + r) *
-                           8 +
-                       tridiag_resident_bytes(n);
+  const size_t ex_words = tridiag_resident_bytes(n) / 8;
+  const size_t res_words = static_cast<size_t>(r + 9 + (r + 7) / 8);
+  const size_t small = (static_cast<size_t>(NB * n + (n + 2 * NB) + 4 * n +
+                                            2 * std::max<int64_t>(npan, 1) * NB * NB + r * NB) +
+                        ex_words + res_words) * 8;
   double* Wp = static_cast<double*>(scratch(kScratchPart, small, stream, &st));
   if (!Wp) return st;
   double* ybv = Wp + NB * n;
@@ -650,18 +608,29 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t 
   double* G = vbuf + n;                                 // [npan][NB][NB]
   double* T = G + std::max<int64_t>(npan, 1) * NB * NB;  // [npan][NB][NB]
   double* X = T + std::max<int64_t>(npan, 1) * NB * NB;
+  double* exch = X + r * NB;
+  double* wd = exch + ex_words;  // eigenvalues
+  double* info = wd + r;
+  int* err = reinterpret_cast<int*>(info + 8);
+  uint8_t* bad = reinterpret_cast<uint8_t*>(info + 9);
+  void* tri = scratch(kScratchD, tri_eigenpairs_bytes(n, r), stream, &st);
+  if (!tri) return st;
+  std::vector<double> res;
+  try {
+    res.resize(res_words);
+  } catch (...) {
+    return fail(BITSMOE_ERR_NOMEM, "shared_basis_gpu: host allocation failed");
+  }
   hipError_t he;
   // 1. tridiagonal reduction: in one launch where the matrix fits the
   // register files (n <= 2048 on 256 compute units; 28.9 -> 6.4 ms at n =
   // 2048), else a panel at a time
-  int* resident_err = nullptr;
   bool resident = tridiag_resident_fits(n);
   if (resident) {
     KernelTimer timer("eig_tridiag", stream);
-    resident = tridiag_resident(M_dev, n, A, dvec, evec, tau, X + r * NB + r, &resident_err, stream);
+    resident = tridiag_resident(M_dev, n, A, dvec, evec, tau, exch, err, stream);
   }
   if (!resident) {
-    resident_err = nullptr;
     he = hipMemcpyAsync(A, M_dev, static_cast<size_t>(n * n) * 8, hipMemcpyDeviceToDevice, s);
     if (he != hipSuccess) return device_error("shared_basis_gpu: copy of M", he);
     KernelTimer timer("eig_tridiag", stream);
@@ -688,90 +657,81 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t 
     hipLaunchKernelGGL(last_diag_kernel, dim3(1), dim3(64), 0, s, A, n, dvec);
   }
   BITSMOE_LAUNCH_CHECK("shared_basis_gpu: tridiagonal reduction");
-  // 2. eigenpairs of T: bounds and clusters on the host, the rest on the device
-  std::vector<double> dh, eh, w;
+  // 2. eigenpairs of T
+  {
+    KernelTimer timer("eig_tri_solve", stream);
+    st = tri_eigenpairs(dvec, evec, n, r, wd, Zt, info, bad, tri, stream);
+    if (st != BITSMOE_OK) return st;
+  }
+  if (npan > 0) {  // (the panels' compact forms, while the host reads the eigenvalues)
+    KernelTimer timer("eig_backtransform", stream);
+    hipLaunchKernelGGL(panel_gram_kernel, dim3(NB / 8, static_cast<unsigned>(npan)), dim3(256), 0, s,
+                       A, n, G);
+    hipLaunchKernelGGL(tfactor_kernel, dim3(static_cast<unsigned>(npan)), dim3(64), 0, s, G, tau, n, T);
+    BITSMOE_LAUNCH_CHECK("shared_basis_gpu: compact forms");
+  }
+  he = hipMemcpyAsync(res.data(), wd, res_words * 8, hipMemcpyDeviceToHost, s);
+  if (he == hipSuccess) he = hipStreamSynchronize(s);
+  if (he != hipSuccess) return device_error("shared_basis_gpu: copy of the eigenvalues", he);
+  const double* w = res.data();
+  const double* info_h = w + r;
+  const uint8_t* bad_h = reinterpret_cast<const uint8_t*>(info_h + 9);
+  if (resident) {
+    int e = 0;
+    std::memcpy(&e, info_h + 8, sizeof e);
+    if (e)
+      return fail(BITSMOE_ERR_DEVICE, "shared_basis_gpu: the tridiagonal reduction's workgroups lost contact");
+  }
+  if (info_h[6] != 0.0) return fail(BITSMOE_ERR_NUMERIC, "shared_basis_gpu: M is not finite");
+  // Vectors of clustered eigenvalues (closer than 1e-7 of the norm: a twisted
+  // factorization gives them the same direction) and those that came out not
+  // finite: inverse iteration, and orthogonalization within each cluster
+  // (bounds as indices into the list).
+  std::vector<int64_t> list, bounds;
   try {
-    dh.resize(static_cast<size_t>(n));
-    eh.resize(static_cast<size_t>(n));
-    w.resize(static_cast<size_t>(r));
+    for (int64_t k = 0; k < r;) {
+      int64_t k1 = k + 1;
+      while (k1 < r && w[k1] - w[k1 - 1] < 1e-7 * info_h[3]) ++k1;
+      if (k1 - k > 1) {
+        bounds.push_back(static_cast<int64_t>(list.size()));
+        for (int64_t q = k; q < k1; ++q) list.push_back(q);
+        bounds.push_back(static_cast<int64_t>(list.size()));
+      } else if (bad_h[k]) {
+        list.push_back(k);
+      }
+      k = k1;
+    }
   } catch (...) {
     return fail(BITSMOE_ERR_NOMEM, "shared_basis_gpu: host allocation failed");
   }
-  int err_host = 0;
-  he = hipMemcpyAsync(dh.data(), dvec, n * 8, hipMemcpyDeviceToHost, s);
-  if (he == hipSuccess && resident_err)
-    he = hipMemcpyAsync(&err_host, resident_err, sizeof err_host, hipMemcpyDeviceToHost, s);
-  if (he == hipSuccess) he = hipMemcpyAsync(eh.data(), evec, n * 8, hipMemcpyDeviceToHost, s);
-  if (he == hipSuccess) he = hipStreamSynchronize(s);
-  if (he != hipSuccess) return device_error("shared_basis_gpu: copy of the tridiagonal", he);
-  if (err_host)
-    return fail(BITSMOE_ERR_DEVICE, "shared_basis_gpu: the tridiagonal reduction's workgroups lost contact");
-  double lo = 0.0, hi = 0.0, tnorm = 0.0, emax2 = 0.0;
-  for (int64_t j = 0; j < n; ++j) {
-    const double dj = dh[static_cast<size_t>(j)];
-    const double el = j > 0 ? std::fabs(eh[static_cast<size_t>(j - 1)]) : 0.0;
-    const double er = j + 1 < n ? std::fabs(eh[static_cast<size_t>(j)]) : 0.0;
-    if (!std::isfinite(dj) || !std::isfinite(el) || !std::isfinite(er))
-      return fail(BITSMOE_ERR_NUMERIC, "shared_basis_gpu: M is not finite");
-    lo = j == 0 ? dj - el - er : std::min(lo, dj - el - er);  // Gershgorin
-    hi = j == 0 ? dj + el + er : std::max(hi, dj + el + er);
-    tnorm = std::max(tnorm, std::fabs(dj) + el + er);
-    emax2 = std::max(emax2, er * er);
-  }
-  const double eps = 2.220446049250313e-16;
-  const double pivmin = 2.2250738585072014e-308 * std::max(1.0, emax2);
-  lo -= 2.0 * eps * tnorm + 2.0 * pivmin;
-  hi += 2.0 * eps * tnorm + 2.0 * pivmin;
-  double* Zn = static_cast<double*>(scratch(kScratchD, static_cast<size_t>(5 * r * n) * 8, stream, &st));
-  if (!Zn) return st;
-  double* work = Zn + r * n;
-  double* wd = X + r * NB;  // eigenvalues, after X in the small buffer
-  {
-    KernelTimer timer("eig_tri_solve", stream);
-    const unsigned g = static_cast<unsigned>((r + 63) / 64);
-    hipLaunchKernelGGL(bisect_kernel, dim3(static_cast<unsigned>((r + 3) / 4)), dim3(256), 0, s, dvec,
-                       evec, n, r, n - r, lo, hi, pivmin, 2.0 * eps * tnorm, wd);
-    hipLaunchKernelGGL(inviter_kernel, dim3(g), dim3(64), 0, s, dvec, evec, n, r, wd, pivmin, work,
-                       Zn);
-  }
-  BITSMOE_LAUNCH_CHECK("shared_basis_gpu: tridiagonal eigenpairs");
-  he = hipMemcpyAsync(w.data(), wd, r * 8, hipMemcpyDeviceToHost, s);
-  if (he == hipSuccess) he = hipStreamSynchronize(s);
-  if (he != hipSuccess) return device_error("shared_basis_gpu: copy of the eigenvalues", he);
-  std::vector<int64_t> clusters;
-  for (int64_t k = 0; k < r;) {
-    int64_t k1 = k + 1;
-    while (k1 < r && w[static_cast<size_t>(k1)] - w[static_cast<size_t>(k1 - 1)] < 1e-7 * tnorm) ++k1;
-    if (k1 - k > 1) {
-      clusters.push_back(k);
-      clusters.push_back(k1);
-    }
-    k = k1;
-  }
-  if (!clusters.empty()) {
-    int64_t* cd = reinterpret_cast<int64_t*>(
-        scratch(kScratchMisc, clusters.size() * 8, stream, &st));
-    if (!cd) return st;
-    he = hipMemcpyAsync(cd, clusters.data(), clusters.size() * 8, hipMemcpyHostToDevice, s);
-    if (he == hipSuccess) he = hipStreamSynchronize(s);  // clusters (host) may go away
+  if (!list.empty()) {
+    const int64_t rc = static_cast<int64_t>(list.size());
+    const double pivmin = 2.2250738585072014e-308 * std::max(1.0, info_h[4]);
+    double* Zn = static_cast<double*>(scratch(kScratchD, static_cast<size_t>(5 * rc * n) * 8, stream, &st));
+    if (!Zn) return st;
+    int64_t* list_d = static_cast<int64_t*>(
+        scratch(kScratchMisc, (list.size() + bounds.size()) * 8, stream, &st));
+    if (!list_d) return st;
+    int64_t* bounds_d = list_d + rc;
+    he = hipMemcpyAsync(list_d, list.data(), list.size() * 8, hipMemcpyHostToDevice, s);
+    if (he == hipSuccess && !bounds.empty())
+      he = hipMemcpyAsync(bounds_d, bounds.data(), bounds.size() * 8, hipMemcpyHostToDevice, s);
+    if (he == hipSuccess) he = hipStreamSynchronize(s);  // the host lists may go away
     if (he != hipSuccess) return device_error("shared_basis_gpu: copy of the clusters", he);
     KernelTimer timer("eig_tri_solve", stream);
-    hipLaunchKernelGGL(mgs_kernel, dim3(static_cast<unsigned>(clusters.size() / 2)), dim3(256), 0, s,
-                       Zn, n, r, cd);
+    hipLaunchKernelGGL(inviter_kernel, dim3(static_cast<unsigned>((rc + 63) / 64)), dim3(64), 0, s, dvec,
+                       evec, n, rc, wd, list_d, pivmin, Zn + rc * n, Zn);
+    if (!bounds.empty())
+      hipLaunchKernelGGL(mgs_kernel, dim3(static_cast<unsigned>(bounds.size() / 2)), dim3(256), 0, s,
+                         Zn, n, rc, bounds_d);
+    hipLaunchKernelGGL(scatter_kernel,
+                       dim3(static_cast<unsigned>((n + 31) / 32), static_cast<unsigned>((rc + 31) / 32)),
+                       dim3(256), 0, s, Zn, n, rc, list_d, Zt);
   }
-  hipLaunchKernelGGL(transpose_kernel,
-                     dim3(static_cast<unsigned>((n + 31) / 32), static_cast<unsigned>((r + 31) / 32)),
-                     dim3(256), 0, s, Zn, n, r, Zt);
   BITSMOE_LAUNCH_CHECK("shared_basis_gpu: cluster orthogonalization");
   // 3. back-transformation, last panel first
   {
     KernelTimer timer("eig_backtransform", stream);
-    if (npan > 0) {
-      hipLaunchKernelGGL(panel_gram_kernel, dim3(NB / 8, static_cast<unsigned>(npan)), dim3(256), 0,
-                         s, A, n, G);
-      hipLaunchKernelGGL(tfactor_kernel, dim3(static_cast<unsigned>(npan)), dim3(64), 0, s, G, tau, n,
-                         T);
-    }
     for (int64_t p = npan - 1; p >= 0; --p) {
       const int64_t j0 = p * NB;
       const int nbp = static_cast<int>(std::min<int64_t>(j0 + NB, n - 1) - j0);
@@ -791,7 +751,7 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t 
   he = hipStreamSynchronize(s);
   if (he != hipSuccess) return device_error("shared_basis_gpu: synchronize", he);
   if (eigvals_host)
-    for (int64_t k = 0; k < r; ++k) eigvals_host[k] = w[static_cast<size_t>(r - 1 - k)];
+    for (int64_t k = 0; k < r; ++k) eigvals_host[k] = w[r - 1 - k];
   if (host_ms) {
     auto t1 = std::chrono::steady_clock::now();
     *host_ms = std::chrono::duration<double, std::milli>(t1 - t0).count();

@@ -54,13 +54,22 @@ class KernelTimer {
 // Tridiagonal reduction of the symmetric fp64 M [n][n] in one cooperative
 // launch (tridiag.hip): the diagonals d [n] and e [n-1], tau [n-1] and the
 // reflectors by rows into V [n][n].  `fits`: whether this device holds an
-// n x n matrix that way; `work` has `bytes` bytes, *err_dev (in it) is
-// nonzero after a run that failed.  False if the launch was refused (nothing
-// was computed).
+// n x n matrix that way; `work` has `bytes` bytes, *err is nonzero after a
+// run that failed.  False if the launch was refused (nothing was computed).
 bool tridiag_resident_fits(int64_t n);
 size_t tridiag_resident_bytes(int64_t n);
 bool tridiag_resident(const double* M, int64_t n, double* V, double* dvec, double* evec,
-                      double* tau, void* work, int** err_dev, void* stream);
+                      double* tau, void* work, int* err, void* stream);
+
+// The r largest eigenvalues w [r] (ascending) of the tridiagonal (d, e) and
+// their eigenvectors, the rows of Zt [r][n] (trieig.hip).  info [7]: scaled
+// bounds (2) and norm, then the norm of T, max e^2, exponent of the scale and
+// 1 if an entry is not finite; bad [r]: 1 where no vector was found.  `buf`
+// has `bytes` bytes.  Vectors of eigenvalues closer than about 1e-7 of the
+// norm are not orthogonal to full precision.
+size_t tri_eigenpairs_bytes(int64_t n, int64_t r);
+bitsmoe_status tri_eigenpairs(const double* d, const double* e, int64_t n, int64_t r, double* w,
+                              double* Zt, double* info, uint8_t* bad, void* buf, void* stream);
 
 // True when every pointer is 16-byte aligned (the kernels use 16-byte
 // vector accesses on device buffers).

@@ -284,17 +284,15 @@ bool tridiag_resident_fits(int64_t n) {
 }
 
 size_t tridiag_resident_bytes(int64_t n) {
-  return n <= kMaxSize ? static_cast<size_t>(6 * n) * 8 + 16 : 0;
+  return n <= kMaxSize ? static_cast<size_t>(6 * n) * 8 : 0;
 }
 
 bool tridiag_resident(const double* M, int64_t n64, double* V, double* dvec, double* evec,
-                      double* tau, void* work, int** err_dev, void* stream) {
+                      double* tau, void* work, int* err, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   int n = static_cast<int>(n64);
   uint64_t* ex = static_cast<uint64_t*>(work);
   const int words = 2 * 3 * n;
-  int* err = reinterpret_cast<int*>(ex + words);
-  *err_dev = err;
   // Four waves up to n = 1024 (with eight, what every wave forms for itself
   // costs more than a second wave per SIMD hides: 768: 2.5 against 3.0 us per
   // column), eight above, where eight columns a lane no longer fit beside the
