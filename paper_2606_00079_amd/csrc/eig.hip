@@ -30,8 +30,8 @@
 //      per eigenvector, three solves from a hashed start vector) and are made
 //      orthonormal by modified Gram-Schmidt (mgs_kernel); others are
 //      orthogonal to about eps ||T|| / gap.
-//   3. Back-transformation U = Q Z = H_0 H_1 ... H_{n-2} Z, one panel at a
-//      time from the last, with the compact form H_j0 ... H_{j0+nb-1} =
+//   3. Back-transformation U = Q Z = H_0 H_1 ... H_{n-2} Z: up to n = 2048 in
+//      one launch (eigback.hip), beyond one panel at a time from the last, with the compact form H_j0 ... H_{j0+nb-1} =
 //      I - V T V^T (T upper triangular from tau and V V^T).
 //   4. Eigenvalues in descending order, each eigenvector signed so that its
 //      entry of largest magnitude is positive (lowest index on ties), fp32.
@@ -663,7 +663,14 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t 
     st = tri_eigenpairs(dvec, evec, n, r, wd, Zt, info, bad, tri, stream);
     if (st != BITSMOE_OK) return st;
   }
-  if (npan > 0) {  // (the panels' compact forms, while the host reads the eigenvalues)
+  // The panels' compact forms, while the host reads the eigenvalues.  Up to
+  // n = 2048 a workgroup holds whole vectors in registers (6.2 -> 0.96 ms).
+  const bool small_back = backtransform_fits(n);
+  if (small_back) {
+    KernelTimer timer("eig_backtransform", stream);
+    st = backtransform_panels(A, tau, n, T, stream);
+    if (st != BITSMOE_OK) return st;
+  } else {
     KernelTimer timer("eig_backtransform", stream);
     hipLaunchKernelGGL(panel_gram_kernel, dim3(NB / 8, static_cast<unsigned>(npan)), dim3(256), 0, s,
                        A, n, G);
@@ -730,7 +737,11 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t 
   }
   BITSMOE_LAUNCH_CHECK("shared_basis_gpu: cluster orthogonalization");
   // 3. back-transformation, last panel first
-  {
+  if (small_back) {
+    KernelTimer timer("eig_backtransform", stream);
+    st = backtransform(A, T, Zt, n, r, Ut_dev, stream);
+    if (st != BITSMOE_OK) return st;
+  } else {
     KernelTimer timer("eig_backtransform", stream);
     for (int64_t p = npan - 1; p >= 0; --p) {
       const int64_t j0 = p * NB;

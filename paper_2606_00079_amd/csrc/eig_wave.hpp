@@ -91,4 +91,13 @@ __device__ __forceinline__ double wave_fold(double (&v)[N], int lane) {
   return v[0];
 }
 
+// Barrier of the workgroup that publishes LDS writes only: __syncthreads()
+// would also wait for global loads and stores in flight (about a microsecond).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0) alone
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 }  // namespace bitsmoe

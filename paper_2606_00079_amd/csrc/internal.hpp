@@ -71,6 +71,17 @@ size_t tri_eigenpairs_bytes(int64_t n, int64_t r);
 bitsmoe_status tri_eigenpairs(const double* d, const double* e, int64_t n, int64_t r, double* w,
                               double* Zt, double* info, uint8_t* bad, void* buf, void* stream);
 
+// Back-transformation of the eigenvectors Zt [r][n] of the tridiagonal by the
+// reflectors V, tau of the reduction, with order, sign and fp32 rounding, into
+// Ut [r][n] (eigback.hip), for n that `fits`.  `panels` forms the compact
+// factors T (`bytes` bytes) first.
+bool backtransform_fits(int64_t n);
+size_t backtransform_bytes(int64_t n);
+bitsmoe_status backtransform_panels(const double* V, const double* tau, int64_t n, double* T,
+                                    void* stream);
+bitsmoe_status backtransform(const double* V, const double* T, const double* Zt, int64_t n, int64_t r,
+                             float* Ut, void* stream);
+
 // True when every pointer is 16-byte aligned (the kernels use 16-byte
 // vector accesses on device buffers).
 inline bool aligned16(std::initializer_list<const void*> ptrs) {

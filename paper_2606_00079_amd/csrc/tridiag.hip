@@ -57,16 +57,6 @@ __global__ __launch_bounds__(256) void tridiag_clear_kernel(uint64_t* __restrict
   if (i == 0) *err = 0;
 }
 
-// Barrier of the workgroup that publishes LDS writes only: __syncthreads()
-// would also wait for the stores to V and to the exchange in flight (about a
-// microsecond each).
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0) alone
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 __device__ __forceinline__ uint64_t load_word(const uint64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
