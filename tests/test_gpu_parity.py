@@ -347,6 +347,22 @@ def test_pack_surrogate_widths_bit_exact(group, d):
     assert np.array_equal(xh.astype(np.float64), oracle.unpack(rc, rp, bits_u, d, group))
 
 
+@pytest.mark.parametrize("group,d", [(64, 64), (64, 320), (256, 256), (32, 544 + 32), (64, 1088)])
+def test_unpack_every_width(group, d):
+    """Rows of less than, exactly and more than whole 256-entry chunks, every
+    width, and a unit count that leaves a workgroup partly empty."""
+    say("unpack every width", group, d)
+    bits_u = np.array([0, 1, 2, 3, 4, 5, 6, 7, 8, 16, 7, 5, 3], dtype=np.uint8)
+    units = len(bits_u)
+    C = synth.random_rows(units, d, seed=d, scale=0.04, heavy=True)
+    rc, rp, off = oracle.pack(C, bits_u, group)
+    bd, od = torch.from_numpy(bits_u).to(DEV), torch.from_numpy(off).to(DEV)
+    codes = torch.from_numpy(rc.view(np.int64)).to(DEV)
+    params = torch.from_numpy(rp.view(np.int16)).to(DEV)
+    xh = bm.unpack(codes, params, bd, od, units, d, group, int(off[-1])).cpu().numpy()
+    assert np.array_equal(xh.astype(np.float64), oracle.unpack(rc, rp, bits_u, d, group))
+
+
 # -------------------------------------------------------------- end to end
 def _stagewise(proj, check_ilp=True):
     """Run the pipeline and check each stage on the device's own inputs:
