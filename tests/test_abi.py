@@ -98,6 +98,36 @@ def test_allocate_core_path_mid_size(lib):
     assert core < U // 4
 
 
+@pytest.mark.parametrize("kind", ["equal", "near", "gap", "spread"])
+def test_allocate_order_of_equal_slopes(lib, kind):
+    """The order of the fixing's greedy where it is hard to decide: all slopes
+    equal, slopes that differ by one unit of the integer costs (less than
+    the fp64 quotients resolve), a critical segment too wide for what is
+    left with much narrower ones far below it, and slopes over 30 decades.
+    The plain dynamic program over all units decides what is right."""
+    g = np.random.default_rng(77)
+    for U in (1, 2, 3, 40, 333):
+        bits = [1, 2, 4, 8]
+        save = np.array([0.0, 1.0, 3.0, 7.0])
+        if kind == "equal":
+            s = np.ones(U)
+        elif kind == "near":
+            s = 1.0 + g.integers(0, 3, U) * 2.0**-23
+        elif kind == "gap":
+            bits, save = [1, 2, 9, 16], np.array([0.0, 1e-6, 7.0, 7.0 + 7e-6])
+            s = np.ones(U)
+        else:
+            s = 10.0 ** g.uniform(-30, 0, U)
+        L = (s[:, None] * (8.0 - save[None])).astype(np.float32)
+        for budget in {U, U + 1, 2 * U, 3 * U + 1, 5 * U + 2, bits[-1] * U - 1, bits[-1] * U}:
+            if budget < U:
+                continue
+            ref, ro, _ = pkg.allocate(L, bits, budget, full_dp_limit=1 << 40, return_core=True)
+            for kw in ({}, {"full_dp_limit": 0}):
+                got, obj = pkg.allocate(L, bits, budget, **kw)
+                assert np.array_equal(got, ref) and obj == ro, (U, budget)
+
+
 def _layer_like_L(g, E, r, bits):
     """Costs shaped like a loss table of E experts x r spectral units:
     energy decaying along each expert's spectrum, error falling about 4x per
