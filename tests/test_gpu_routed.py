@@ -64,6 +64,39 @@ def test_gram_routed(config):
     say("max rel fro", max(relfro(Hs[e], ref[e]) for e in experts))
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [64, 256, 320, 576])
+def test_grams_without_split(d, dt):
+    """K loops too short to split: the tiles are written by the GEMM itself
+    (part of a tile, a whole one, two and three tiles a side), for every
+    Gram of the library.  Bound: the products are exact but for the dropped
+    lo x lo term (2^-18) and the rounding of w x to two bf16 terms (2^-17),
+    and at most 64 terms are added in fp32 (64 x 2^-24)."""
+    say("grams without split", d, dt)
+    g = np.random.default_rng(d)
+    X = synth.random_rows(50, d, seed=d, scale=1.0, heavy=True)
+    Xd = dev(X, "f32") if dt == "f32" else dev(X, "f32").to(torch.bfloat16)
+    X64 = Xd.double().cpu().numpy()
+    bar = 2.0**-17 + 2.0**-18 + 64 * 2.0**-24
+    H = bm.gram(Xd).cpu().numpy()
+    assert np.array_equal(H, H.T) and relfro(H, X64.T @ X64 / 50) <= bar
+    off = np.array([0, 20, 20, 50, 90], dtype=np.int64)
+    tok = g.integers(0, 50, 90).astype(np.int32)
+    w = g.random(90).astype(np.float32)
+    Hs = bm.gram_routed(Xd, off, tok, w).cpu().numpy()
+    ref = routed.gram_routed(X64, off, tok, w)
+    for e in range(4):
+        assert np.array_equal(Hs[e], Hs[e].T) and relfro(Hs[e], ref[e]) <= bar
+    # W of one expert [d][64], M = W W^T in fp64, and the input-space form
+    W = dev(synth.random_rows(d, 64, seed=d + 1, scale=1.0), "f32").to(Xd.dtype)
+    W64 = W.double().cpu().numpy()
+    M = bm.gram_experts(W[None]).cpu().numpy()
+    assert M.dtype == np.float64 and np.array_equal(M, M.T) and relfro(M, W64 @ W64.T) <= bar
+    Wt = W.t().contiguous()
+    Mi = bm.gram_experts_in(Wt[None]).cpu().numpy()
+    assert np.array_equal(Mi, Mi.T) and relfro(Mi, W64 @ W64.T) <= bar
+
+
 def test_gram_routed_empty_expert_and_ragged_rows():
     g = np.random.default_rng(3)
     X = synth.random_rows(150, 192, seed=3, scale=1.0, heavy=True)
