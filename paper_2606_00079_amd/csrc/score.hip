@@ -53,44 +53,59 @@ __device__ __forceinline__ int exponent_above(float v) {
   return v > 0.0f ? e : 0;
 }
 
-// Partial maxima of |H_ik| over the whole matrix (a bound for the
-// off-diagonal maximum), one per block; d * d is a multiple of 4.
+// Partial maxima of |H_ik| over the upper block triangle (H is symmetric: a
+// bound for the off-diagonal maximum), one per block.  Row i counts from
+// its diagonal block on, columns 256 (i / 256) .. d - 1, so a wave takes
+// rows w and d - 1 - w: about the same number of entries for every wave.
 __global__ __launch_bounds__(256) void habsmax_kernel(const float* __restrict__ H, int64_t d,
                                                       float* __restrict__ partial) {
-  __shared__ float red[256];
+  __shared__ float red[4];
   H += static_cast<int64_t>(blockIdx.y) * d * d;  // one H per blockIdx.y
   partial += static_cast<int64_t>(blockIdx.y) * kAbsMaxBlocks;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   float m = 0.0f;
-  const int64_t n4 = d * d / 4;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
-  // four 16-byte loads in flight per thread
-  for (int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; idx < n4;
-       idx += 4 * stride) {
-    float4 v[4];
+  auto row_max = [&](int64_t i) {
+    const float* row = H + i * d;
+    // eight 16-byte loads in flight per lane
+    for (int64_t k0 = i / SBM * SBM; k0 < d; k0 += 8 * 256) {
+      float4 v[8];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      v[q] = idx + q * stride < n4 ? reinterpret_cast<const float4*>(H)[idx + q * stride]
-                                   : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      for (int q = 0; q < 8; ++q) {
+        const int64_t k = k0 + 256 * q + 4 * lane;
+        v[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (k < d) v[q] = *reinterpret_cast<const float4*>(row + k);
+      }
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      m = fmaxf(m, fmaxf(fmaxf(fabsf(v[q].x), fabsf(v[q].y)), fmaxf(fabsf(v[q].z), fabsf(v[q].w))));
+      for (int q = 0; q < 8; ++q)
+        m = fmaxf(m, fmaxf(fmaxf(fabsf(v[q].x), fabsf(v[q].y)), fmaxf(fabsf(v[q].z), fabsf(v[q].w))));
+    }
+  };
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * 4;
+  for (int64_t w = static_cast<int64_t>(blockIdx.x) * 4 + wave; w < (d + 1) / 2; w += stride) {
+    row_max(w);
+    row_max(d - 1 - w);
   }
-  red[threadIdx.x] = m;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  if (lane == 0) red[wave] = m;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + o]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) partial[blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
 // H -> fp16 H_off * 2^F (zero diagonal) in the K-tiled layout of 256-row
 // tiles (rows padded to a multiple of 256 with zeros), and fp32 diag(H).
 // H is symmetric and the GEMM reads only the upper block triangle: row tile
 // t uses column blocks t (weight 1) and t + 1, ... (weight 2, which stands
-// for the mirrored lower blocks); blocks left of the diagonal are never read.
+// for the mirrored lower blocks); blocks left of the diagonal are neither
+// read nor written.  One workgroup per 256 x 32 block of the layout.
 // F = kF16Top - 1 - e(max |H|), so that doubled entries stay below 2^14;
 // block 0 also stores F for the finalize step.
+// Number of blocks at and right of the diagonal of row tiles 0 .. rt - 1.
+__host__ __device__ __forceinline__ int64_t hoff_blocks(int64_t rt, int64_t nkt) {
+  constexpr int64_t per = SBM / gemm::kTileK;
+  return rt * nkt - per * rt * (rt - 1) / 2;
+}
 __global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, int64_t d,
                                                    int64_t d_pad, const float* __restrict__ partial,
                                                    uint16_t* __restrict__ Hoff,
@@ -104,6 +119,26 @@ __global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, 
     hdiag += z * d;
     hexp += z;
   }
+  const int64_t nkt = d / gemm::kTileK;
+  constexpr int64_t TB = static_cast<int64_t>(SBM) * gemm::kTileK;  // elements per tiled block
+  constexpr int kRuns = static_cast<int>(TB / 8 / 256);             // 8-entry runs per thread
+  int64_t rt = 0;
+  while (hoff_blocks(rt + 1, nkt) <= blockIdx.x) ++rt;
+  const int64_t kt = rt * (SBM / gemm::kTileK) + (blockIdx.x - hoff_blocks(rt, nkt));
+  // the loads are issued before the maximum is known
+  float h[kRuns][8];
+#pragma unroll
+  for (int x = 0; x < kRuns; ++x) {
+    const int w = 8 * (static_cast<int>(threadIdx.x) + 256 * x);
+    const int64_t i = rt * SBM + w / gemm::kTileK;
+    const int64_t k = kt * gemm::kTileK + w % gemm::kTileK;
+#pragma unroll
+    for (int q = 0; q < 8; q += 4) {
+      float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (i < d) v = *reinterpret_cast<const float4*>(H + i * d + k + q);
+      h[x][q] = v.x; h[x][q + 1] = v.y; h[x][q + 2] = v.z; h[x][q + 3] = v.w;
+    }
+  }
   if (threadIdx.x < 64) {  // wave 0 reduces the partial maxima
     float m = 0.0f;
     for (int b = threadIdx.x; b < kAbsMaxBlocks; b += 64) m = fmaxf(m, partial[b]);
@@ -115,31 +150,20 @@ __global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, 
     }
   }
   __syncthreads();
-  const int F = sF;
-  // eight consecutive outputs per thread: one row i, entries k .. k+7 of one
-  // K tile and one column block (d is a multiple of 32)
-  const int64_t total8 = d_pad * d / 8;
-  const int64_t nkt = d / gemm::kTileK;
-  constexpr int64_t TB = static_cast<int64_t>(SBM) * gemm::kTileK;  // elements per tiled block
-  for (int64_t c = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; c < total8;
-       c += static_cast<int64_t>(gridDim.x) * 256) {
-    const int64_t idx = 8 * c;
-    const int64_t t = idx / TB, w = idx - t * TB;
-    const int64_t rt = t / nkt, kt = t - rt * nkt;
+  const int e = kt / (SBM / gemm::kTileK) > rt ? sF + 1 : sF;
+  uint16_t* dst = Hoff + (rt * nkt + kt) * TB;
+#pragma unroll
+  for (int x = 0; x < kRuns; ++x) {
+    const int w = 8 * (static_cast<int>(threadIdx.x) + 256 * x);
     const int64_t i = rt * SBM + w / gemm::kTileK;
     const int64_t k = kt * gemm::kTileK + w % gemm::kTileK;
-    uint16_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (i < d && k / SBM >= i / SBM) {  // at or right of the diagonal block
-      const float4 h0 = *reinterpret_cast<const float4*>(H + i * d + k);
-      const float4 h1 = *reinterpret_cast<const float4*>(H + i * d + k + 4);
-      const float h[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
-      const int e = k / SBM > i / SBM ? F + 1 : F;
+    uint16_t v[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        if (i == k + q)
-          hdiag[i] = h[q];
-        else
-          v[q] = f32_to_f16_bits(ldexpf(h[q], e));
+    for (int q = 0; q < 8; ++q) {
+      v[q] = f32_to_f16_bits(ldexpf(h[x][q], e));
+      if (i == k + q) {
+        if (i < d) hdiag[i] = h[x][q];
+        v[q] = 0;
       }
     }
     uint4 pk;
@@ -147,7 +171,7 @@ __global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, 
     pk.y = static_cast<uint32_t>(v[2]) | (static_cast<uint32_t>(v[3]) << 16);
     pk.z = static_cast<uint32_t>(v[4]) | (static_cast<uint32_t>(v[5]) << 16);
     pk.w = static_cast<uint32_t>(v[6]) | (static_cast<uint32_t>(v[7]) << 16);
-    *reinterpret_cast<uint4*>(Hoff + idx) = pk;
+    *reinterpret_cast<uint4*>(dst + w) = pk;
   }
 }
 
@@ -730,14 +754,19 @@ bitsmoe_status loss_table_setup(int64_t d, int64_t R, int64_t units, bool row_st
   return BITSMOE_OK;
 }
 
-// H -> scaled fp16 H_off and diag(H).
+// H -> scaled fp16 H_off and diag(H).  Bound by memory: 128 H of 2048 take
+// 274 us for the maximum and 425 us for H_off (404 and 550 when both went over
+// the whole square).  Taking a few H at a time through both, for the second
+// to find them in the last-level cache, was slower (368 and 369: the launches
+// are too short to run at full bandwidth).
 bitsmoe_status loss_table_hoff(const float* H_dev, const LossTable& t, hipStream_t s, const char* who) {
+  const int64_t blocks = hoff_blocks(t.tiles_m, t.d / gemm::kTileK);
+  if (blocks > INT32_MAX) return fail(BITSMOE_ERR_SHAPE, std::string(who) + ": too many blocks");
   const unsigned nh = static_cast<unsigned>(t.nh);
   hipLaunchKernelGGL(habsmax_kernel, dim3(kAbsMaxBlocks, nh), dim3(256), 0, s, H_dev, t.d, t.hpart);
   BITSMOE_LAUNCH_CHECK(who);
-  const unsigned hb = static_cast<unsigned>(std::min<int64_t>((t.d_pad * t.d / 8 + 255) / 256, 16384));
-  hipLaunchKernelGGL(hoff_kernel, dim3(hb, nh), dim3(256), 0, s, H_dev, t.d, t.d_pad, t.hpart, t.Hoff,
-                     t.hdiag, t.hexp);
+  hipLaunchKernelGGL(hoff_kernel, dim3(static_cast<unsigned>(blocks), nh), dim3(256), 0, s, H_dev,
+                     t.d, t.d_pad, t.hpart, t.Hoff, t.hdiag, t.hexp);
   BITSMOE_LAUNCH_CHECK(who);
   return BITSMOE_OK;
 }
