@@ -7,7 +7,8 @@
 // so iterative subspace methods converge slowly; this is a direct solver:
 //
 //   1. Householder reduction to tridiagonal form, T = Q^T M Q: up to n = 2048
-//      in one launch with the matrix in registers (tridiag.hip), beyond in panels of
+//      in one launch with the matrix in registers (tridiag.hip: of one
+//      workgroup up to 192, of the whole device above), beyond in panels of
 //      NB columns (the blocked scheme of LAPACK's symmetric reduction, lower
 //      form, stored by rows since M is symmetric).  Per column i of a panel:
 //        trsymv_kernel  the reflector H_i = I - tau v v^T that zeroes row i
@@ -624,13 +625,17 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t 
   hipError_t he;
   // 1. tridiagonal reduction: in one launch where the matrix fits the
   // register files (n <= 2048 on 256 compute units; 28.9 -> 6.4 ms at n =
-  // 2048), else a panel at a time
-  bool resident = tridiag_resident_fits(n);
-  if (resident) {
+  // 2048; up to 192 those of one compute unit), else a panel at a time
+  const bool one_cu = tridiag_small_fits(n);
+  bool resident = !one_cu && tridiag_resident_fits(n);
+  if (one_cu) {
+    KernelTimer timer("eig_tridiag", stream);
+    tridiag_small(M_dev, n, A, dvec, evec, tau, stream);
+  } else if (resident) {
     KernelTimer timer("eig_tridiag", stream);
     resident = tridiag_resident(M_dev, n, A, dvec, evec, tau, exch, err, stream);
   }
-  if (!resident) {
+  if (!one_cu && !resident) {
     he = hipMemcpyAsync(A, M_dev, static_cast<size_t>(n * n) * 8, hipMemcpyDeviceToDevice, s);
     if (he != hipSuccess) return device_error("shared_basis_gpu: copy of M", he);
     KernelTimer timer("eig_tridiag", stream);

@@ -61,6 +61,11 @@ size_t tridiag_resident_bytes(int64_t n);
 bool tridiag_resident(const double* M, int64_t n, double* V, double* dvec, double* evec,
                       double* tau, void* work, int* err, void* stream);
 
+// The same by one workgroup, for n that `fits`.
+bool tridiag_small_fits(int64_t n);
+void tridiag_small(const double* M, int64_t n, double* V, double* dvec, double* evec, double* tau,
+                   void* stream);
+
 // The r largest eigenvalues w [r] (ascending) of the tridiagonal (d, e) and
 // their eigenvectors, the rows of Zt [r][n] (trieig.hip).  info [7]: scaled
 // bounds (2) and norm, then the norm of T, max e^2, exponent of the scale and

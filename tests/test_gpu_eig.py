@@ -51,6 +51,18 @@ def _check_invariants(M, Ut, ev, r):
     assert np.linalg.norm(U.T @ U - np.eye(r)) <= 2e-6 * max(1.0, np.sqrt(r))
 
 
+@pytest.mark.parametrize("n,r", [(2, 2), (63, 5), (64, 64), (66, 66), (127, 30), (128, 128), (129, 40),
+                                 (191, 20), (192, 192), (193, 30)])
+def test_reduction_by_one_workgroup_edges(n, r):
+    """Sizes on both sides of each form of the one-workgroup reduction (64
+    columns per lane step, at most 192), with row and column counts that
+    leave its last waves partly empty."""
+    say("one workgroup", n, r)
+    M = _separated(n, seed=3 * n + r)
+    Ut, ev, _ = bm.shared_basis_gpu(torch.from_numpy(M).to(DEV), r)
+    _check_invariants(M, Ut.cpu().numpy(), ev, r)
+
+
 @pytest.mark.parametrize("n,r", [(1, 1), (2, 1), (2, 2), (3, 2), (33, 33), (33, 7), (64, 32),
                                  (65, 65), (100, 37), (257, 128), (300, 1)])
 def test_separated_spectrum_matches_oracle(n, r):
