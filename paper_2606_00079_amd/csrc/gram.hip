@@ -18,39 +18,87 @@ namespace {
 constexpr int GT = 256;  // tile edge of the symmetric GEMMs
 using gemm::BK;
 
+// A 64 x 64 block of rows of X (tokens) is brought into LDS with 16-byte
+// loads, eight channels a thread, and leaves it transposed with 16-byte
+// stores, eight tokens of a channel a thread: four threads cover the 64-byte
+// row that a channel has in a K tile, a wave 1 KiB of the tile.  (The float
+// rows of 65 make the writes of a wave conflict-free and its reads two-way.)
+struct TokenTile {
+  float v[64][65];
+
+  // Row `row` (0 .. 63), channels c0 + 8 chunk ..: from X, or zeros.
+  template <bool F32>
+  __device__ __forceinline__ void load(int row, int chunk, const void* X, int64_t offset, bool valid) {
+    float f[8] = {};
+    if (valid) {
+      if (F32) {
+        const float4* p = reinterpret_cast<const float4*>(static_cast<const float*>(X) + offset);
+        const float4 a = p[0], b = p[1];
+        f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w;
+        f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
+      } else {
+        const uint4 a = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(X) + offset);
+        const uint32_t w[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          f[2 * j] = __uint_as_float(w[j] << 16);
+          f[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[row][8 * chunk + j] = f[j];
+  }
+  // Tokens t .. t + 7 of channel c.
+  __device__ __forceinline__ void read(int t, int c, float (&f)[8]) const {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) f[j] = v[t + j][c];
+  }
+};
+
+// f as bf16 (hi) and what that leaves of it as bf16 (lo), eight of each.
+__device__ __forceinline__ void split8(const float (&f)[8], uint4* hi, uint4* lo) {
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint16_t h0 = f32_to_bf16(f[2 * j]), h1 = f32_to_bf16(f[2 * j + 1]);
+    h[j] = static_cast<uint32_t>(h0) | (static_cast<uint32_t>(h1) << 16);
+    l[j] = static_cast<uint32_t>(f32_to_bf16(f[2 * j] - bf16_to_f32(h0))) |
+           (static_cast<uint32_t>(f32_to_bf16(f[2 * j + 1] - bf16_to_f32(h1))) << 16);
+  }
+  *hi = make_uint4(h[0], h[1], h[2], h[3]);
+  *lo = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
 // X [n][d] -> Xt [d_pad][npad] (bf16) in the K-tiled layout of GT-row tiles
 // (K = tokens), tokens beyond n zero.  For fp32 input the value is split
-// x = hi + lo with hi = bf16(x), lo = bf16(x - hi).
+// x = hi + lo with hi = bf16(x), lo = bf16(x - hi).  4096 x 2048 bf16:
+// 8.2 us, against 15.5 with 2-byte loads and stores.
 template <bool F32>
 __global__ __launch_bounds__(256) void transpose_split_kernel(const void* __restrict__ X, int64_t n,
                                                               int64_t d, int64_t npad,
                                                               uint16_t* __restrict__ hi,
                                                               uint16_t* __restrict__ lo) {
-  __shared__ float tile[64][65];
-  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * 64;  // token block
-  const int64_t c0 = static_cast<int64_t>(blockIdx.y) * 64;  // channel block
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;     // 64 x 4
-  for (int i = ty; i < 64; i += 4) {
-    const int64_t t = t0 + i, c = c0 + tx;
-    float v = 0.0f;
-    if (t < n && c < d) {
-      if (F32)
-        v = static_cast<const float*>(X)[t * d + c];
-      else
-        v = bf16_to_f32(static_cast<const uint16_t*>(X)[t * d + c]);
-    }
-    tile[i][tx] = v;
+  __shared__ TokenTile tile;
+  // token and channel block; npad and d are multiples of 64
+  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * 64, c0 = static_cast<int64_t>(blockIdx.y) * 64;
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int row = 32 * x + (tid >> 3), chunk = tid & 7;
+    tile.load<F32>(row, chunk, X, (t0 + row) * d + c0 + 8 * chunk, t0 + row < n);
   }
   __syncthreads();
-  for (int i = ty; i < 64; i += 4) {
-    const int64_t c = c0 + i, t = t0 + tx;
-    if (c < d && t < npad) {
-      const float v = tile[tx][i];
-      const uint16_t h = f32_to_bf16(v);
-      const int64_t o = gemm::tiled_offset(c, t, npad, GT);
-      hi[o] = h;
-      if (F32) lo[o] = f32_to_bf16(v - bf16_to_f32(h));
-    }
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int c = tid >> 2, t = 32 * x + 8 * (tid & 3);
+    float f[8];
+    tile.read(t, c, f);
+    uint4 h, l;
+    split8(f, &h, &l);
+    const int64_t o = gemm::tiled_offset(c0 + c, t0 + t, npad, GT);
+    *reinterpret_cast<uint4*>(hi + o) = h;
+    if (F32) *reinterpret_cast<uint4*>(lo + o) = l;
   }
 }
 
@@ -71,48 +119,46 @@ __global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ W,
 // symmetric GEMM (rows = channels, K = the expert's tokens, zero-padded to
 // npad): the A side holds x_{rows[i]} (fp32 input split into bf16 hi + lo),
 // the B side w_i x_{rows[i]} split into hi + lo.  Routing entries are
-// checked on the host (rows in [0, n)).
+// checked on the host (rows in [0, n)).  128 experts of 256 tokens of 2048:
+// 109 us for 500 MB, against 182 with 2-byte stores.
 template <bool F32>
 __global__ __launch_bounds__(256) void routed_gather_kernel(
     const void* __restrict__ X, int64_t d, const int64_t* __restrict__ off,
     const int32_t* __restrict__ rows, const float* __restrict__ w, int64_t npad, int64_t d_pad,
     uint16_t* __restrict__ a_hi, uint16_t* __restrict__ a_lo, uint16_t* __restrict__ b_hi,
     uint16_t* __restrict__ b_lo) {
-  __shared__ float tile[64][65];
+  __shared__ TokenTile tile;
   __shared__ float wt[64];
   const int64_t e = blockIdx.z;
   const int64_t i0 = static_cast<int64_t>(blockIdx.x) * 64;  // token block of the expert
   const int64_t c0 = static_cast<int64_t>(blockIdx.y) * 64;  // channel block
   const int64_t o0 = off[e], ne = off[e + 1] - o0;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  if (ty == 0) wt[tx] = (i0 + tx < ne) ? w[o0 + i0 + tx] : 0.0f;
-  for (int i = ty; i < 64; i += 4) {
-    const int64_t t = i0 + i, c = c0 + tx;
-    float v = 0.0f;
-    if (t < ne && c < d) {
-      const int64_t row = rows[o0 + t];
-      if (F32)
-        v = static_cast<const float*>(X)[row * d + c];
-      else
-        v = bf16_to_f32(static_cast<const uint16_t*>(X)[row * d + c]);
-    }
-    tile[i][tx] = v;
+  const int tid = threadIdx.x;
+  if (tid < 64) wt[tid] = (i0 + tid < ne) ? w[o0 + i0 + tid] : 0.0f;
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int row = 32 * x + (tid >> 3), chunk = tid & 7;
+    const bool valid = i0 + row < ne;
+    const int64_t src = valid ? rows[o0 + i0 + row] : 0;
+    tile.load<F32>(row, chunk, X, src * d + c0 + 8 * chunk, valid);
   }
   __syncthreads();
   const int64_t base = e * d_pad * npad;
-  for (int i = ty; i < 64; i += 4) {
-    const int64_t c = c0 + i, t = i0 + tx;
-    if (c < d) {
-      const float v = tile[tx][i];
-      const int64_t o = base + gemm::tiled_offset(c, t, npad, GT);
-      const uint16_t h = f32_to_bf16(v);
-      a_hi[o] = h;
-      if (F32) a_lo[o] = f32_to_bf16(v - bf16_to_f32(h));
-      const float wv = wt[tx] * v;
-      const uint16_t hb = f32_to_bf16(wv);
-      b_hi[o] = hb;
-      b_lo[o] = f32_to_bf16(wv - bf16_to_f32(hb));
-    }
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int c = tid >> 2, t = 32 * x + 8 * (tid & 3);
+    float f[8];
+    tile.read(t, c, f);
+    const int64_t o = base + gemm::tiled_offset(c0 + c, i0 + t, npad, GT);
+    uint4 h, l;
+    split8(f, &h, &l);
+    *reinterpret_cast<uint4*>(a_hi + o) = h;
+    if (F32) *reinterpret_cast<uint4*>(a_lo + o) = l;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) f[j] *= wt[t + j];
+    split8(f, &h, &l);
+    *reinterpret_cast<uint4*>(b_hi + o) = h;
+    *reinterpret_cast<uint4*>(b_lo + o) = l;
   }
 }
 
