@@ -277,6 +277,29 @@ __global__ __launch_bounds__(256) void decode_z_kernel(
   }
 }
 
+// Entry k of token b's z: the sum, in slot order, of its partial rows
+// zp[slot][k], slots b kmax + j (pidx null) or pidx[b kmax + j] (-1: none).
+// Eight slots' loads are in flight at a time.
+__device__ __forceinline__ float token_sum(const float* __restrict__ zp,
+                                           const int64_t* __restrict__ pidx, int kmax, int r,
+                                           int64_t b, int k) {
+  float s = 0.0f;
+  for (int j0 = 0; j0 < kmax; j0 += 8) {
+    int64_t i[8];
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      i[q] = -1;
+      if (j0 + q < kmax) i[q] = pidx ? pidx[b * kmax + j0 + q] : b * kmax + j0 + q;
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = i[q] >= 0 ? zp[i[q] * r + k] : 0.0f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s += v[q];
+  }
+  return s;
+}
+
 // y[b][o] = sum_k Ut[k][o] z_b[k], z_b[k] = sum over token b's routing
 // entries (in the order given) of zp[i][k]: the entries pidx[b][0..kmax)
 // (-1 = none), or b kmax .. b kmax + kmax - 1 when pidx is null.  TB tokens per workgroup
@@ -312,14 +335,7 @@ __global__ __launch_bounds__(1024) void decode_y_kernel(const float* __restrict_
   for (int idx = threadIdx.x; idx < TB * rp; idx += 64 * kYWaves) {
     const int tb = idx / rp, k = idx - tb * rp;
     const int64_t b = b0 + tb;
-    float s = 0.0f;
-    if (b < B && k < r) {
-      for (int j = 0; j < kmax; ++j) {
-        const int64_t i = pidx ? pidx[b * kmax + j] : b * kmax + j;
-        if (i >= 0) s += zp[i * r + k];
-      }
-    }
-    z[idx] = s;
+    z[idx] = b < B && k < r ? token_sum(zp, pidx, kmax, r, b, k) : 0.0f;
   }
   __syncthreads();
   float acc[TB];
@@ -808,8 +824,13 @@ __global__ __launch_bounds__(64 * WV) void decode_zmma_kernel(
 }
 
 // Z[b][k] for b < Bp, k < rp (zero past B and r) = the sum, in slot order,
-// of the token's partial rows zp[slot][k]: slots b kmax + j (pidx null) or
-// pidx[b kmax + j] (-1: none).
+// of the token's partial rows zp[slot][k] (token_sum), in the order in which
+// decode_ymma reads it: 1 KiB blocks of 16 tokens x 16 k's, block (k / 16)
+// (Bp / 16) + b / 16, and within it 16 bytes (four k's) of token b % 16 at
+// piece 16 ((k / 4) % 4) + b % 16.
+__device__ __forceinline__ int64_t z_block(int64_t b, int k, int64_t Bp) {
+  return ((k >> 4) * (Bp >> 4) + (b >> 4)) * 256 + (((k >> 2) & 3) * 16 + (b & 15)) * 4 + (k & 3);
+}
 __global__ __launch_bounds__(256) void zsum_kernel(const float* __restrict__ zp,
                                                    const int64_t* __restrict__ pidx, int kmax,
                                                    int r, int rp, int64_t B, int64_t Bp,
@@ -818,45 +839,43 @@ __global__ __launch_bounds__(256) void zsum_kernel(const float* __restrict__ zp,
   if (idx >= Bp * rp) return;
   const int64_t b = idx / rp;
   const int k = static_cast<int>(idx - b * rp);
-  float s = 0.0f;
-  if (b < B && k < r) {
-    for (int j = 0; j < kmax; ++j) {
-      const int64_t i = pidx ? pidx[b * kmax + j] : b * kmax + j;
-      if (i >= 0) s += zp[i * r + k];
-    }
-  }
-  Z[idx] = s;
+  Z[z_block(b, k, Bp)] = b < B && k < r ? token_sum(zp, pidx, kmax, r, b, k) : 0.0f;
 }
 
-// Y[b][o] = sum_k Z[b][k] U^T[k][o] for the 64 tokens of blockIdx.y and the
+// Y[b][o] = sum_k Z[b][k] U^T[k][o] for the 16 MT tokens of blockIdx.y and the
 // 16 columns of blockIdx.x as v_mfma_f32_16x16x4_f32 (A = Z, tokens as M;
 // B = U^T, columns as N), the 16 waves splitting k into ranges of kw (a
-// multiple of 16; Z [Bp][rp] is zero past r) and their sums added in wave
+// multiple of 16; Z is zero past r) and their sums added in wave
 // order through LDS.  Within 16 k's, lane l supplies k = 4 (l / 16) + i at
-// sub-step i, so that its four Z values are one float4.
+// sub-step i, so that its four Z values are one float4 and a wave's are one
+// contiguous KiB (from rows of Z they were sixteen half cache lines, and their
+// requests bound the step).  MT = 2 where 64 tokens a workgroup would leave
+// compute units idle: U is read twice then, from L2.  64 tokens of 1024 x 2048:
+// 7.2 us, against 13.3.
 constexpr int kYmmaWaves = 16;
+template <int MT>
 __global__ __launch_bounds__(64 * kYmmaWaves) void decode_ymma_kernel(
     const float* __restrict__ Z, int rp, int r, int kw, const float* __restrict__ Ut,
-    int64_t d_out, int64_t B, float* __restrict__ Y) {
-  __shared__ float red[kYmmaWaves][16][64];
+    int64_t d_out, int64_t B, int64_t Bp, float* __restrict__ Y) {
+  __shared__ float red[kYmmaWaves][4 * MT][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int tau = lane & 15, c = lane >> 4;
   const int64_t o = static_cast<int64_t>(blockIdx.x) * 16 + tau;
-  const int64_t b0 = static_cast<int64_t>(blockIdx.y) * 64;
+  const int64_t b0 = static_cast<int64_t>(blockIdx.y) * (16 * MT);
   const int k0 = wave * kw, k1 = min(k0 + kw, rp);
-  float4v acc[4];
+  float4v acc[MT];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) acc[m] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int m = 0; m < MT; ++m) acc[m] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
   // 64 k's at a time: every load of the four 16-k chunks before their MFMAs
   for (int kb0 = k0; kb0 < k1; kb0 += 64) {
-    float4 a[4][4];
+    float4 a[4][MT];
     float bv[4][4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int kb = kb0 + 16 * u;
 #pragma unroll
-      for (int m = 0; m < 4; ++m)
-        a[u][m] = kb < k1 ? *reinterpret_cast<const float4*>(Z + (b0 + 16 * m + tau) * rp + kb + 4 * c)
+      for (int m = 0; m < MT; ++m)
+        a[u][m] = kb < k1 ? *reinterpret_cast<const float4*>(Z + z_block(b0 + 16 * m + tau, kb + 4 * c, Bp))
                           : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -869,18 +888,19 @@ __global__ __launch_bounds__(64 * kYmmaWaves) void decode_ymma_kernel(
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
+        for (int m = 0; m < MT; ++m) {
           const float4 am = a[u][m];
           const float av = i == 0 ? am.x : i == 1 ? am.y : i == 2 ? am.z : am.w;
           acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[u][i], acc[m], 0, 0, 0);
         }
   }
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int i = 0; i < 4; ++i) red[wave][4 * m + i][lane] = acc[m][i];
   __syncthreads();
   const int j = threadIdx.x >> 6, ln = threadIdx.x & 63;
+  if (j >= 4 * MT) return;  // whole wave
   float sum = 0.0f;
 #pragma unroll
   for (int w = 0; w < kYmmaWaves; ++w) sum += red[w][j][ln];
@@ -1381,9 +1401,15 @@ bitsmoe_status decode_mma(const uint32_t* c32, const uint32_t* pr, const uint8_t
     hipLaunchKernelGGL(zsum_kernel, dim3(static_cast<unsigned>((nz + 255) / 256)), dim3(256), 0, s,
                        zp, pidx_d, kmax, static_cast<int>(r), static_cast<int>(m.rp), B, m.Bp, Zs);
     const int kw = static_cast<int>((m.rp / 16 + kYmmaWaves - 1) / kYmmaWaves * 16);
-    dim3 grid(static_cast<unsigned>((d_out + 15) / 16), static_cast<unsigned>(m.Bp / 64));
-    hipLaunchKernelGGL(decode_ymma_kernel, grid, dim3(64 * kYmmaWaves), 0, s, Zs,
-                       static_cast<int>(m.rp), static_cast<int>(r), kw, Ut_dev, d_out, B, Y_dev);
+    const int64_t cols = (d_out + 15) / 16;
+    if (cols * (m.Bp / 64) < device_cus())
+      hipLaunchKernelGGL(decode_ymma_kernel<2>, dim3(static_cast<unsigned>(cols), static_cast<unsigned>((B + 31) / 32)),
+                         dim3(64 * kYmmaWaves), 0, s, Zs, static_cast<int>(m.rp), static_cast<int>(r), kw,
+                         Ut_dev, d_out, B, m.Bp, Y_dev);
+    else
+      hipLaunchKernelGGL(decode_ymma_kernel<4>, dim3(static_cast<unsigned>(cols), static_cast<unsigned>(m.Bp / 64)),
+                         dim3(64 * kYmmaWaves), 0, s, Zs, static_cast<int>(m.rp), static_cast<int>(r), kw,
+                         Ut_dev, d_out, B, m.Bp, Y_dev);
   }
   BITSMOE_LAUNCH_CHECK("moe_decode: y launch");
   return ok();
