@@ -24,6 +24,7 @@
 //     sum_j (q_j s + m) x_j = s sum_j q_j x_j + m sum_j x_j.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -911,135 +912,229 @@ __global__ __launch_bounds__(64 * kYmmaWaves) void decode_ymma_kernel(
 
 // ---- input-space form (gate/up): y = sum_j g_j C^_e^T z, z = Phi_r^T x ----
 
-// z[b][k] = sum_i Vt[k][i] X[b][i]: one wave per (k, b).
+// z[b][k] = sum_i Vt[k][i] X[b][i]: one wave per row k and four tokens, so
+// that a row of the basis is read once for them, with 16-byte loads where
+// the rows allow it (VEC: d_in % 4 == 0).  At r = 384, d_in = 2048 and 23
+// tokens 7.0 us, against 8.0 for a wave per (k, token) and 4-byte loads.
+constexpr int kZinTokens = 4;
+template <bool VEC>
 __global__ __launch_bounds__(256) void zin_kernel(const float* __restrict__ Vt, int r, int64_t d_in,
                                                   const float* __restrict__ X, int64_t B,
                                                   float* __restrict__ z) {
+  constexpr int N = kZinTokens;
   const int lane = threadIdx.x & 63;
   const int64_t k = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  const int64_t b = blockIdx.y;
-  if (k >= r || b >= B) return;  // whole wave
+  const int64_t b0 = static_cast<int64_t>(blockIdx.y) * N;
+  if (k >= r) return;  // whole wave
   const float* v = Vt + k * d_in;
-  const float* x = X + b * d_in;
-  float acc = 0.0f;
+  const float* x[N];
+#pragma unroll
+  for (int t = 0; t < N; ++t) x[t] = X + (b0 + t < B ? b0 + t : b0) * d_in;
+  float acc[N] = {};
+  if constexpr (VEC) {
 #pragma unroll 4
-  for (int64_t i = lane; i < d_in; i += 64) acc = fmaf(v[i], x[i], acc);
-  acc = wave_sum(acc);
-  if (lane == 0) z[b * r + k] = acc;
+    for (int64_t i = 4 * lane; i < d_in; i += 256) {
+      const float4 a = *reinterpret_cast<const float4*>(v + i);
+#pragma unroll
+      for (int t = 0; t < N; ++t) {
+        const float4 c = *reinterpret_cast<const float4*>(x[t] + i);
+        acc[t] = fmaf(a.x, c.x, acc[t]);
+        acc[t] = fmaf(a.y, c.y, acc[t]);
+        acc[t] = fmaf(a.z, c.z, acc[t]);
+        acc[t] = fmaf(a.w, c.w, acc[t]);
+      }
+    }
+  } else {
+#pragma unroll 4
+    for (int64_t i = lane; i < d_in; i += 64) {
+      const float a = v[i];
+#pragma unroll
+      for (int t = 0; t < N; ++t) acc[t] = fmaf(a, x[t][i], acc[t]);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < N; ++t) {
+    const float s = wave_sum(acc[t]);
+    if (lane == 0 && b0 + t < B) z[(b0 + t) * r + k] = s;
+  }
 }
 
 // Partial outputs of the routing entries of one job (blockIdx.y; jobs[2j] =
 // {expert, first entry, entries 1..T, 0}, jobs[2j+1] = their tokens) over the
 // unit rows of row split blockIdx.z:
 //   yp[rz][i][o] = w_i sum_{k in split} z[tok_i][k] c^_{e,k}[o].
-// Thread (slice rs, segment sg) owns the 32 outputs 32 sg .. 32 sg + 31 of
+// Thread (slice rs, segment sg) owns the 16 outputs 16 sg .. 16 sg + 15 of
 // segment block blockIdx.x and the rows k = rs, rs + RSL, ... of the split;
-// a unit row's 32 entries there are one word of each of its bit planes and
+// a unit row's 16 entries there are half a word of each of its bit planes and
 // one group parameter, so c^ = q s + m is summed as (z s) q and z m.  The
 // RSL slices are added in slice order through LDS.
+//
+// The step is bound by its chains of loads (job, width and offset, planes),
+// not by bytes (7.5 MB at 23 tokens of a 384 x 768 projection): the rows'
+// descriptors and z are staged in LDS for up to 256 rows at once, and the
+// planes of a thread's next row are loaded while the current one is summed.
+// Sixteen outputs a thread leave registers for several waves per SIMD beside
+// that (32 with the prefetch took 312 and 52 us), the sums run over the
+// tokens the job has, slices are as many as the segments leave room for (SEGW
+// need not be a power of two), and the LDS rows of the reduction are padded to
+// 17 words (unpadded, all lanes of a store hit a few banks).  22.4 us there,
+// against 28.5 with 32 outputs, four tokens always, and the loads in a row's
+// own iteration.
+constexpr int kInSeg = 16;  // outputs per thread
 template <int T>
 __global__ __launch_bounds__(256) void yin_kernel(
     const uint32_t* __restrict__ codes32, const uint32_t* __restrict__ params,
     const uint8_t* __restrict__ bits, const int64_t* __restrict__ off, int64_t total_words,
-    int r, int d, int G, int SEGW, int rows_split, const float* __restrict__ z,
+    int r, int d, int gshift, int SEGW, int rows_split, const float* __restrict__ z,
     const int4* __restrict__ jobs, const float* __restrict__ ew, int64_t nnz,
     float* __restrict__ yp) {
-  __shared__ float red[256 * kSeg];
+  constexpr int kPad = kInSeg + 1;
+  __shared__ float red[256 * kPad];
+  __shared__ int64_t s_o[256];
+  __shared__ int s_b[256];
+  __shared__ float s_z[T][256];
   const int4 job = jobs[2 * blockIdx.y];
   const int4 jt = jobs[2 * blockIdx.y + 1];
   const int e = job.x;
   const int64_t i0 = job.y;
-  const int nt = job.z;
   const int tk[4] = {jt.x, jt.y, jt.z, jt.w};
   const int RSL = 256 / SEGW;
-  const int sg_local = threadIdx.x % SEGW, rs = threadIdx.x / SEGW;
-  const int nseg = d / kSeg;
+  const int rs = static_cast<int>(threadIdx.x) / SEGW, sg_local = static_cast<int>(threadIdx.x) - rs * SEGW;
+  const int nseg = d / kInSeg;
   const int sg = static_cast<int>(blockIdx.x) * SEGW + sg_local;
-  const int64_t nw = d / 64;
+  const int nw = d / 64;
   const int kb = static_cast<int>(blockIdx.z) * rows_split;
   const int ke = min(r, kb + rows_split);
-  float acc[T][kSeg], macc[T];
+  const bool mine = rs < RSL && sg < nseg;
+  // the job's first NT tokens
+  auto body = [&]<int NT>() {
+    float acc[NT][kInSeg], macc[NT];
 #pragma unroll
-  for (int t = 0; t < T; ++t) {
-    macc[t] = 0.0f;
+    for (int t = 0; t < NT; ++t) {
+      macc[t] = 0.0f;
 #pragma unroll
-    for (int j = 0; j < kSeg; ++j) acc[t][j] = 0.0f;
-  }
-  if (sg < nseg) {
-    for (int k = kb + rs; k < ke; k += RSL) {
-      const int64_t u = static_cast<int64_t>(e) * r + k;
-      const int b = bits[u];
-      const int64_t o0 = off[u], o1 = off[u + 1];
-      // a unit whose width or offsets are inconsistent contributes nothing
-      if (!(width_ok(b) && b != 0 && o1 - o0 == b * nw && o0 >= 0 && o1 <= total_words)) continue;
-      float zk[T];
-#pragma unroll
-      for (int t = 0; t < T; ++t) zk[t] = t < nt ? z[static_cast<int64_t>(tk[t]) * r + k] : 0.0f;
-      if (b == 16) {
-        const uint2* h = reinterpret_cast<const uint2*>(codes32 + 2 * o0) + 8 * sg;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const uint2 v = h[q];
-          const float c[4] = {f16_bits_to_f32(static_cast<uint16_t>(v.x & 0xffffu)),
-                              f16_bits_to_f32(static_cast<uint16_t>(v.x >> 16)),
-                              f16_bits_to_f32(static_cast<uint16_t>(v.y & 0xffffu)),
-                              f16_bits_to_f32(static_cast<uint16_t>(v.y >> 16))};
-#pragma unroll
-          for (int c4 = 0; c4 < 4; ++c4)
-#pragma unroll
-            for (int t = 0; t < T; ++t) acc[t][4 * q + c4] = fmaf(zk[t], c[c4], acc[t][4 * q + c4]);
-        }
-        continue;
-      }
-      const uint32_t prm = params[u * (d / G) + (sg * kSeg) / G];
-      const float s = f16_bits_to_f32(static_cast<uint16_t>(prm & 0xffffu));
-      const float m = f16_bits_to_f32(static_cast<uint16_t>(prm >> 16));
-      const uint32_t* pw = codes32 + 2 * o0 + sg;  // plane t: word 2 (o0 + t nw) + sg
-      uint32_t qb[kSeg / 4];
-      {
-        const uint32_t p0 = pw[0];
-#pragma unroll
-        for (int kk = 0; kk < kSeg / 4; ++kk) qb[kk] = spread4(p0 >> (4 * kk));
-      }
-      for (int t = 1; t < b; ++t) {
-        const uint32_t pt = pw[2 * t * nw];
-#pragma unroll
-        for (int kk = 0; kk < kSeg / 4; ++kk) qb[kk] |= spread4(pt >> (4 * kk)) << t;
-      }
-      float zs[T];
-#pragma unroll
-      for (int t = 0; t < T; ++t) {
-        zs[t] = zk[t] * s;
-        macc[t] = fmaf(zk[t], m, macc[t]);
-      }
-#pragma unroll
-      for (int kk = 0; kk < kSeg / 4; ++kk)
-#pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) {
-          const float q = static_cast<float>((qb[kk] >> (8 * c4)) & 0xffu);
-#pragma unroll
-          for (int t = 0; t < T; ++t) acc[t][4 * kk + c4] = fmaf(zs[t], q, acc[t][4 * kk + c4]);
-        }
+      for (int j = 0; j < kInSeg; ++j) acc[t][j] = 0.0f;
     }
-  }
-  // slices in order, one token at a time: red[rs][sg_local][j]
+    // planes and parameter of the thread's row q of the staged ones
+    struct Row {
+      int b;
+      uint32_t pw[BITSMOE_MAX_BITS];
+      uint32_t prm;
+    };
+    auto fetch = [&](int kc, int n, int q, Row& f) {
+      f.b = mine && q < n ? s_b[q] : 0;
+      if (f.b >= 1 && f.b <= BITSMOE_MAX_BITS) {
+        // plane t of the segment: half word 4 (o0 + t nw) + sg
+        const uint16_t* pw = reinterpret_cast<const uint16_t*>(codes32) + 4 * s_o[q] + sg;
 #pragma unroll
-  for (int t = 0; t < T; ++t) {
-    if (t >= nt) continue;  // uniform over the workgroup
-    __syncthreads();
+        for (int t = 0; t < BITSMOE_MAX_BITS; ++t)
+          if (t < f.b) f.pw[t] = pw[4 * t * nw];
+        f.prm = params[((static_cast<int64_t>(e) * r + kc + q) * d + sg * kInSeg) >> gshift];
+      }
+    };
+    for (int kc = kb; kc < ke; kc += 256) {
+      const int n = min(256, ke - kc);
+      __syncthreads();
+      if (static_cast<int>(threadIdx.x) < n) {
+        const int k = kc + static_cast<int>(threadIdx.x);
+        const int64_t u = static_cast<int64_t>(e) * r + k;
+        const int b = bits[u];
+        const int64_t o0 = off[u], o1 = off[u + 1];
 #pragma unroll
-    for (int j = 0; j < kSeg; ++j) red[(rs * SEGW + sg_local) * kSeg + j] = acc[t][j] + macc[t];
-    __syncthreads();
-    const float wt = ew[i0 + t];
-    for (int idx = threadIdx.x; idx < SEGW * kSeg; idx += 256) {
-      const int sgl = idx / kSeg, j = idx - sgl * kSeg;
-      const int sgo = static_cast<int>(blockIdx.x) * SEGW + sgl;
-      if (sgo >= nseg) continue;
-      float v = 0.0f;
-      for (int q = 0; q < RSL; ++q) v += red[(q * SEGW + sgl) * kSeg + j];
-      yp[(static_cast<int64_t>(blockIdx.z) * nnz + i0 + t) * d + static_cast<int64_t>(sgo) * kSeg + j] =
-          wt * v;
+        for (int t = 0; t < NT; ++t)
+          s_z[t][threadIdx.x] = t < job.z ? z[static_cast<int64_t>(tk[t]) * r + k] : 0.0f;
+        // a unit whose width or offsets are inconsistent contributes nothing
+        const bool valid = width_ok(b) && o1 - o0 == static_cast<int64_t>(b) * nw && o0 >= 0 && o1 <= total_words;
+        s_b[threadIdx.x] = valid ? b : 0;
+        s_o[threadIdx.x] = valid ? o0 : 0;
+      }
+      __syncthreads();
+      Row cur, nxt;
+      fetch(kc, n, rs, cur);
+      for (int q0 = 0; q0 < n; q0 += RSL) {
+        const int q = q0 + rs;
+        fetch(kc, n, q + RSL, nxt);
+        if (cur.b == 16) {
+          const uint2* h = reinterpret_cast<const uint2*>(codes32 + 2 * s_o[q]) + 4 * sg;
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const uint2 v = h[g];
+            const float c[4] = {f16_bits_to_f32(static_cast<uint16_t>(v.x & 0xffffu)),
+                                f16_bits_to_f32(static_cast<uint16_t>(v.x >> 16)),
+                                f16_bits_to_f32(static_cast<uint16_t>(v.y & 0xffffu)),
+                                f16_bits_to_f32(static_cast<uint16_t>(v.y >> 16))};
+#pragma unroll
+            for (int c4 = 0; c4 < 4; ++c4)
+#pragma unroll
+              for (int t = 0; t < NT; ++t)
+                acc[t][4 * g + c4] = fmaf(s_z[t][q], c[c4], acc[t][4 * g + c4]);
+          }
+        } else if (cur.b != 0) {
+          const float s = f16_bits_to_f32(static_cast<uint16_t>(cur.prm & 0xffffu));
+          const float m = f16_bits_to_f32(static_cast<uint16_t>(cur.prm >> 16));
+          float zs[NT];
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            const float zk = s_z[t][q];
+            zs[t] = zk * s;
+            macc[t] = fmaf(zk, m, macc[t]);
+          }
+          uint32_t qb[kInSeg / 4];
+#pragma unroll
+          for (int kk = 0; kk < kInSeg / 4; ++kk) qb[kk] = spread4(cur.pw[0] >> (4 * kk));
+#pragma unroll
+          for (int t = 1; t < BITSMOE_MAX_BITS; ++t) {
+            if (t < cur.b) {
+#pragma unroll
+              for (int kk = 0; kk < kInSeg / 4; ++kk) qb[kk] |= spread4_at((cur.pw[t] >> (4 * kk)) & 15u, t);
+            }
+          }
+#pragma unroll
+          for (int kk = 0; kk < kInSeg / 4; ++kk)
+#pragma unroll
+            for (int c4 = 0; c4 < 4; ++c4) {
+              const float qv = static_cast<float>((qb[kk] >> (8 * c4)) & 0xffu);
+#pragma unroll
+              for (int t = 0; t < NT; ++t) acc[t][4 * kk + c4] = fmaf(zs[t], qv, acc[t][4 * kk + c4]);
+            }
+        }
+        cur = nxt;
+      }
     }
+    // slices in order, one token at a time: red[rs][sg_local][j]
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (t >= job.z) continue;  // uniform over the workgroup
+      __syncthreads();
+      if (rs < RSL) {
+#pragma unroll
+        for (int j = 0; j < kInSeg; ++j) red[(rs * SEGW + sg_local) * kPad + j] = acc[t][j] + macc[t];
+      }
+      __syncthreads();
+      const float wt = ew[i0 + t];
+      for (int idx = threadIdx.x; idx < SEGW * kInSeg; idx += 256) {
+        const int sgl = idx / kInSeg, j = idx - sgl * kInSeg;
+        const int sgo = static_cast<int>(blockIdx.x) * SEGW + sgl;
+        if (sgo >= nseg) continue;
+        float v = 0.0f;
+        for (int q = 0; q < RSL; ++q) v += red[(q * SEGW + sgl) * kPad + j];
+        yp[(static_cast<int64_t>(blockIdx.z) * nnz + i0 + t) * d + static_cast<int64_t>(sgo) * kInSeg + j] =
+            wt * v;
+      }
+    }
+  };
+  if constexpr (T == 1) {
+    body.template operator()<1>();
+  } else if constexpr (T == 2) {
+    if (job.z == 1)
+      body.template operator()<1>();
+    else
+      body.template operator()<2>();
+  } else {
+    if (job.z <= 2)
+      body.template operator()<2>();
+    else
+      body.template operator()<T>();
   }
 }
 
@@ -1191,12 +1286,12 @@ bitsmoe_status upload_routing(const std::string& who, const RoutingTables& rt,
   *pidx_d = reinterpret_cast<int64_t*>(tab + job_bytes);
   *w_d = reinterpret_cast<float*>(tab + job_bytes + pidx_bytes);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t he = hipSuccess;
-  if (rt.njobs > 0) he = hipMemcpyAsync(*jobs_d, rt.jobs.data(), rt.njobs * 32, hipMemcpyHostToDevice, s);
-  if (he == hipSuccess)
-    he = hipMemcpyAsync(*pidx_d, rt.pidx.data(), B * rt.kmax * 8, hipMemcpyHostToDevice, s);
-  if (he == hipSuccess && rt.nnz > 0)
-    he = hipMemcpyAsync(*w_d, weights_host, rt.nnz * 4, hipMemcpyHostToDevice, s);
+  // one copy for the three tables
+  std::vector<char> host(job_bytes + pidx_bytes + w_bytes, 0);
+  if (rt.njobs > 0) std::memcpy(host.data(), rt.jobs.data(), static_cast<size_t>(rt.njobs) * 32);
+  std::memcpy(host.data() + job_bytes, rt.pidx.data(), pidx_bytes);
+  if (rt.nnz > 0) std::memcpy(host.data() + job_bytes + pidx_bytes, weights_host, static_cast<size_t>(rt.nnz) * 4);
+  hipError_t he = hipMemcpyAsync(tab, host.data(), host.size(), hipMemcpyHostToDevice, s);
   if (he == hipSuccess) he = hipStreamSynchronize(s);
   if (he != hipSuccess) return device_error((who + ": routing table copy").c_str(), he);
   return ok();
@@ -1629,20 +1724,21 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
   if (st != BITSMOE_OK) return st;
   if (d_in > (1 << 20)) return fail(BITSMOE_ERR_SHAPE, "moe_decode_in: d_in above 2^20");
   RoutingTables rt;
-  st = build_routing("moe_decode_in", E, B, offsets_host, tokens_host, weights_host, 4, &rt);
+  // Tokens per job: four share a decoded row, at 186 registers (two waves per
+  // SIMD); two (118 registers) while the experts with entries have at most two on
+  // average, when most of the four would go unused.
+  int64_t busy = 0;
+  if (offsets_host)
+    for (int64_t e = 0; e < E; ++e) busy += offsets_host[e + 1] > offsets_host[e] ? 1 : 0;
+  const int tmax = offsets_host && offsets_host[E] <= 2 * busy ? 2 : 4;
+  st = build_routing("moe_decode_in", E, B, offsets_host, tokens_host, weights_host, tmax, &rt);
   if (st != BITSMOE_OK) return st;
-  int4* jobs_d;
-  int64_t* pidx_d;
-  float* w_d;
-  st = upload_routing("moe_decode_in", rt, weights_host, B, stream, &jobs_d, &pidx_d, &w_d);
-  if (st != BITSMOE_OK) return st;
-  // segments of 32 outputs: SEGW per workgroup (a power of two up to 256),
-  // RSL = 256 / SEGW row slices; rows split over blockIdx.z for about 1024
-  // workgroups but at least four rows per thread (each split adds a partial
-  // per output to the final sum)
-  const int64_t nseg = d_out / kSeg;
-  int SEGW = 2;
-  while (SEGW < nseg && SEGW < 256) SEGW *= 2;
+  // segments of 16 outputs: SEGW per workgroup (up to 256), RSL = 256 / SEGW
+  // row slices; rows split over blockIdx.z for about 1024 workgroups but at
+  // least four rows per thread (each split adds a partial per output to the
+  // final sum; half as many splits moved 3 us from the sum to the rows)
+  const int64_t nseg = d_out / kInSeg;
+  const int SEGW = static_cast<int>(std::min<int64_t>(nseg, 256));
   const int RSL = 256 / SEGW;
   const int64_t segblocks = (nseg + SEGW - 1) / SEGW;
   int64_t nsplit = std::clamp<int64_t>(1024 / std::max<int64_t>(rt.njobs * segblocks, 1), 1,
@@ -1661,10 +1757,20 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
   hipStream_t s = static_cast<hipStream_t>(stream);
   {
     KernelTimer timer("moe_decode_in_z", stream);
-    hipLaunchKernelGGL(zin_kernel, dim3(static_cast<unsigned>((r + 3) / 4), static_cast<unsigned>(B)),
-                       dim3(256), 0, s, Vt_dev, static_cast<int>(r), d_in, X_dev, B, z);
+    const dim3 grid(static_cast<unsigned>((r + 3) / 4),
+                    static_cast<unsigned>((B + kZinTokens - 1) / kZinTokens));
+    if (d_in % 4 == 0)
+      hipLaunchKernelGGL(zin_kernel<true>, grid, dim3(256), 0, s, Vt_dev, static_cast<int>(r), d_in, X_dev, B, z);
+    else
+      hipLaunchKernelGGL(zin_kernel<false>, grid, dim3(256), 0, s, Vt_dev, static_cast<int>(r), d_in, X_dev, B, z);
   }
   BITSMOE_LAUNCH_CHECK("moe_decode_in: z launch");
+  // the basis product runs while the host copies the routing tables
+  int4* jobs_d;
+  int64_t* pidx_d;
+  float* w_d;
+  st = upload_routing("moe_decode_in", rt, weights_host, B, stream, &jobs_d, &pidx_d, &w_d);
+  if (st != BITSMOE_OK) return st;
   const uint32_t* pr = reinterpret_cast<const uint32_t*>(params_dev);
   const uint32_t* c32 = reinterpret_cast<const uint32_t*>(codes_dev);
   if (rt.njobs > 0) {
@@ -1673,9 +1779,9 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
               static_cast<unsigned>(nsplit));
 #define BITSMOE_DECIN(TT)                                                                           \
   hipLaunchKernelGGL(yin_kernel<TT>, grid, dim3(256), 0, s, c32, pr, bits_dev, word_offsets_dev,    \
-                     total_words, static_cast<int>(r), static_cast<int>(d_out), group, SEGW,        \
+                     total_words, static_cast<int>(r), static_cast<int>(d_out), __builtin_ctz(group), SEGW, \
                      static_cast<int>(rows_split), z, jobs_d, w_d, rt.nnz, yp)
-    if (rt.T == 4) BITSMOE_DECIN(4); else BITSMOE_DECIN(1);
+    if (rt.T == 4) BITSMOE_DECIN(4); else if (rt.T == 2) BITSMOE_DECIN(2); else BITSMOE_DECIN(1);
 #undef BITSMOE_DECIN
   }
   BITSMOE_LAUNCH_CHECK("moe_decode_in: y launch");

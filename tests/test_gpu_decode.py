@@ -230,6 +230,30 @@ def _run_in(E, r, d_out, d_in, B, k, G, widths, seed):
 
 
 @pytest.mark.parametrize("E,r,d_out,d_in,B,k,G,widths", [
+    (32, 21, 320, 70, 9, 2, 64, (0, 1, 3, 5, 6, 7, 8, 16)),  # jobs of two, 20 of 256 / 12 slices, d_in % 4 != 0
+    (32, 300, 64, 302, 6, 3, 32, (1, 2, 16)),                # jobs of two, 4 segments a row, two row blocks
+    (2, 600, 2048, 604, 7, 2, 256, (2, 3, 8)),               # jobs of four (last of three), three row blocks
+    (3, 5, 4160, 64, 2, 1, 64, (1, 4)),                      # two segment blocks, the second nearly empty
+])
+def test_moe_decode_in_edges(E, r, d_out, d_in, B, k, G, widths):
+    """Both job sizes, ragged slices and segments, rows in several blocks."""
+    say("decode_in edges", E, r, d_out, d_in, B, k, G, widths)
+    Y, ref = _run_in(E, r, d_out, d_in, B, k, G, widths, seed=E + r + B)
+    assert relfro(Y, ref) <= REL
+
+
+@pytest.mark.parametrize("B", [16, 32, 33, 64, 65, 100])
+@pytest.mark.parametrize("d_out", [80, 4160])
+def test_moe_decode_y_tiles(B, d_out):
+    """Token counts around the 32 and 64 tokens of a y workgroup, both tile
+    heights (few and many columns), r not a multiple of 16."""
+    say("decode y tiles", B, d_out)
+    Y, Yg, ref = _topk_run(6, 37, 128, d_out, B, 2, 64, (1, 2, 3, 4), seed=B + d_out)
+    assert_close(Y, ref)
+    assert_close(Yg, ref)
+
+
+@pytest.mark.parametrize("E,r,d_out,d_in,B,k,G,widths", [
     (4, 64, 128, 256, 24, 2, 64, (1, 2, 3, 4)),
     (6, 40, 192, 96, 17, 3, 32, (0, 1, 2, 4, 8, 16)),   # eviction and fp16 rows
     (3, 8, 64, 768, 1, 1, 32, (2, 3)),                  # 64-entry units, one token
