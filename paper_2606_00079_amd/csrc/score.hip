@@ -14,7 +14,7 @@
 // are scaled back by 2^-(2 E_u + F).  (bf16 operands, 8-bit precision, leave
 // per-entry errors close to 1e-3 on strongly correlated H; fp16 keeps them
 // near 1e-4 at the same matrix-core rate.)
-//   1. habsmax_kernel, hoff_kernel
+//   1. hdiagmax_kernel, hoff_kernel, hoff_redo_kernel
 //                    H -> scaled fp16 H_off (zero diagonal), fp32 diag(H)
 //   2. dgen_kernel   one wave per unit: max |c_u|, group min/max, fake-quant
 //                    at every width, scaled fp16 error rows D[u*nb + j][:] and
@@ -43,7 +43,6 @@ constexpr int SKB = 32;   // K step of the loss-table GEMM
 constexpr int SSTAGES = 4;  // LDS stages (two K tiles in flight)
 using gemm::BK;
 
-constexpr int kAbsMaxBlocks = 256;  // partial maxima of |H_off|
 constexpr int kF16Top = 14;         // scaled fp16 operands stay below 2^14
 
 // Exponent e with 0 <= v < 2^e (v finite, >= 0); 0 for v == 0.
@@ -53,44 +52,32 @@ __device__ __forceinline__ int exponent_above(float v) {
   return v > 0.0f ? e : 0;
 }
 
-// Partial maxima of |H_ik| over the upper block triangle (H is symmetric: a
-// bound for the off-diagonal maximum), one per block.  Row i counts from
-// its diagonal block on, columns 256 (i / 256) .. d - 1, so a wave takes
-// rows w and d - 1 - w: about the same number of entries for every wave.
-__global__ __launch_bounds__(256) void habsmax_kernel(const float* __restrict__ H, int64_t d,
-                                                      float* __restrict__ partial) {
-  __shared__ float red[4];
-  H += static_cast<int64_t>(blockIdx.y) * d * d;  // one H per blockIdx.y
-  partial += static_cast<int64_t>(blockIdx.y) * kAbsMaxBlocks;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+// The scale 2^F of H_off comes from max |H|: F = kF16Top - 1 - e(max |H|), so
+// that doubled entries stay below 2^14.  The largest entry of a Gram is on its
+// diagonal, so hdiagmax_kernel looks there only, hoff_kernel converts with
+// that F and checks every entry it reads against the bound 2^e, and
+// hoff_redo_kernel does the matrices again whose check failed (symmetric but not
+// semidefinite) with the maximum over the upper block triangle.  F is that of
+// the whole matrix in every case.
+struct HMax {
+  float diag;         // max |H_ii|
+  uint32_t above;     // bits of the largest |H_ik| at or above the bound, 0: none
+};
+__global__ __launch_bounds__(1024) void hdiagmax_kernel(const float* __restrict__ H, int64_t d,
+                                                        HMax* __restrict__ hmax) {
+  __shared__ float red[16];
+  H += static_cast<int64_t>(blockIdx.x) * d * d;  // one H per workgroup
   float m = 0.0f;
-  auto row_max = [&](int64_t i) {
-    const float* row = H + i * d;
-    // eight 16-byte loads in flight per lane
-    for (int64_t k0 = i / SBM * SBM; k0 < d; k0 += 8 * 256) {
-      float4 v[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int64_t k = k0 + 256 * q + 4 * lane;
-        v[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (k < d) v[q] = *reinterpret_cast<const float4*>(row + k);
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        m = fmaxf(m, fmaxf(fmaxf(fabsf(v[q].x), fabsf(v[q].y)), fmaxf(fabsf(v[q].z), fabsf(v[q].w))));
-    }
-  };
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * 4;
-  for (int64_t w = static_cast<int64_t>(blockIdx.x) * 4 + wave; w < (d + 1) / 2; w += stride) {
-    row_max(w);
-    row_max(d - 1 - w);
-  }
+#pragma unroll 4
+  for (int64_t i = threadIdx.x; i < d; i += 1024) m = fmaxf(m, fabsf(H[i * d + i]));
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-  if (lane == 0) red[wave] = m;
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0) partial[blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) m = fmaxf(m, red[w]);
+    hmax[blockIdx.x] = HMax{m, 0u};
+  }
 }
 
 // H -> fp16 H_off * 2^F (zero diagonal) in the K-tiled layout of 256-row
@@ -98,34 +85,21 @@ __global__ __launch_bounds__(256) void habsmax_kernel(const float* __restrict__ 
 // H is symmetric and the GEMM reads only the upper block triangle: row tile
 // t uses column blocks t (weight 1) and t + 1, ... (weight 2, which stands
 // for the mirrored lower blocks); blocks left of the diagonal are neither
-// read nor written.  One workgroup per 256 x 32 block of the layout.
-// F = kF16Top - 1 - e(max |H|), so that doubled entries stay below 2^14;
-// block 0 also stores F for the finalize step.
+// read nor written.  `bx` counts the 256 x 32 blocks of the layout.
 // Number of blocks at and right of the diagonal of row tiles 0 .. rt - 1.
 __host__ __device__ __forceinline__ int64_t hoff_blocks(int64_t rt, int64_t nkt) {
   constexpr int64_t per = SBM / gemm::kTileK;
   return rt * nkt - per * rt * (rt - 1) / 2;
 }
-__global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, int64_t d,
-                                                   int64_t d_pad, const float* __restrict__ partial,
-                                                   uint16_t* __restrict__ Hoff,
-                                                   float* __restrict__ hdiag, int* __restrict__ hexp) {
-  __shared__ int sF;
-  {  // one H per blockIdx.y
-    const int64_t z = blockIdx.y;
-    H += z * d * d;
-    partial += z * kAbsMaxBlocks;
-    Hoff += z * d_pad * d;
-    hdiag += z * d;
-    hexp += z;
-  }
+// Returns the largest |H_ik| this thread read.
+__device__ __forceinline__ float hoff_block(const float* __restrict__ H, int64_t d, int64_t bx, int F,
+                                            uint16_t* __restrict__ Hoff, float* __restrict__ hdiag) {
   const int64_t nkt = d / gemm::kTileK;
   constexpr int64_t TB = static_cast<int64_t>(SBM) * gemm::kTileK;  // elements per tiled block
   constexpr int kRuns = static_cast<int>(TB / 8 / 256);             // 8-entry runs per thread
   int64_t rt = 0;
-  while (hoff_blocks(rt + 1, nkt) <= blockIdx.x) ++rt;
-  const int64_t kt = rt * (SBM / gemm::kTileK) + (blockIdx.x - hoff_blocks(rt, nkt));
-  // the loads are issued before the maximum is known
+  while (hoff_blocks(rt + 1, nkt) <= bx) ++rt;
+  const int64_t kt = rt * (SBM / gemm::kTileK) + (bx - hoff_blocks(rt, nkt));
   float h[kRuns][8];
 #pragma unroll
   for (int x = 0; x < kRuns; ++x) {
@@ -139,19 +113,9 @@ __global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, 
       h[x][q] = v.x; h[x][q + 1] = v.y; h[x][q + 2] = v.z; h[x][q + 3] = v.w;
     }
   }
-  if (threadIdx.x < 64) {  // wave 0 reduces the partial maxima
-    float m = 0.0f;
-    for (int b = threadIdx.x; b < kAbsMaxBlocks; b += 64) m = fmaxf(m, partial[b]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    if (threadIdx.x == 0) {
-      sF = kF16Top - 1 - exponent_above(m);
-      if (blockIdx.x == 0) *hexp = sF;
-    }
-  }
-  __syncthreads();
-  const int e = kt / (SBM / gemm::kTileK) > rt ? sF + 1 : sF;
+  const int e = kt / (SBM / gemm::kTileK) > rt ? F + 1 : F;
   uint16_t* dst = Hoff + (rt * nkt + kt) * TB;
+  float m = 0.0f;
 #pragma unroll
   for (int x = 0; x < kRuns; ++x) {
     const int w = 8 * (static_cast<int>(threadIdx.x) + 256 * x);
@@ -160,6 +124,7 @@ __global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, 
     uint16_t v[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
+      m = fmaxf(m, fabsf(h[x][q]));
       v[q] = f32_to_f16_bits(ldexpf(h[x][q], e));
       if (i == k + q) {
         if (i < d) hdiag[i] = h[x][q];
@@ -173,6 +138,32 @@ __global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, 
     pk.w = static_cast<uint32_t>(v[6]) | (static_cast<uint32_t>(v[7]) << 16);
     *reinterpret_cast<uint4*>(dst + w) = pk;
   }
+  return m;
+}
+__global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, int64_t d,
+                                                   int64_t d_pad, HMax* __restrict__ hmax,
+                                                   uint16_t* __restrict__ Hoff,
+                                                   float* __restrict__ hdiag, int* __restrict__ hexp) {
+  const int64_t z = blockIdx.y;  // one H per blockIdx.y
+  const float dm = hmax[z].diag;
+  const int e = exponent_above(dm);
+  const int F = kF16Top - 1 - e;
+  if (blockIdx.x == 0 && threadIdx.x == 0) hexp[z] = F;
+  const float m = hoff_block(H + z * d * d, d, blockIdx.x, F, Hoff + z * d_pad * d, hdiag + z * d);
+  // (a zero diagonal bounds nothing: any entry has to be looked at)
+  const float bound = dm > 0.0f ? ldexpf(1.0f, e) : 0.0f;
+  if (m >= bound && m > 0.0f) atomicMax(&hmax[z].above, __float_as_uint(m));
+}
+__global__ __launch_bounds__(256) void hoff_redo_kernel(const float* __restrict__ H, int64_t d,
+                                                        int64_t d_pad, const HMax* __restrict__ hmax,
+                                                        int64_t blocks, uint16_t* __restrict__ Hoff,
+                                                        float* __restrict__ hdiag, int* __restrict__ hexp) {
+  const int64_t z = blockIdx.y;
+  if (hmax[z].above == 0u) return;  // whole workgroup
+  const int F = kF16Top - 1 - exponent_above(fmaxf(hmax[z].diag, __uint_as_float(hmax[z].above)));
+  if (blockIdx.x == 0 && threadIdx.x == 0) hexp[z] = F;
+  for (int64_t bx = blockIdx.x; bx < blocks; bx += gridDim.x)
+    (void)hoff_block(H + z * d * d, d, bx, F, Hoff + z * d_pad * d, hdiag + z * d);
 }
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -712,7 +703,7 @@ struct LossTable {
   float* hdiag;  // [d]
   float* diag;   // [R]
   int* uexp;     // [units]
-  float* hpart;  // [kAbsMaxBlocks]
+  HMax* hmax;    // [nh]
   int* hexp;     // [nh]
   float* rstats; // [3 units] (surrogate only)
   float* part;   // [R][tiles_m]
@@ -735,17 +726,17 @@ bitsmoe_status loss_table_setup(int64_t d, int64_t R, int64_t units, bool row_st
   t->Hoff = static_cast<uint16_t*>(scratch(kScratchA, nh * t->d_pad * d * 2, stream, &st));
   if (!t->Hoff) return st;
   // small tables: diag(H) [nh][d], diagonal terms [R], unit exponents
-  // [units], partial maxima of |H_off| [nh][kAbsMaxBlocks], the H_off
-  // exponents [nh], row statistics [3 units]
+  // [units], maxima of |H| [nh], the H_off exponents [nh], row statistics
+  // [3 units]
   const int64_t small_words =
-      nh * d + R + units + nh * kAbsMaxBlocks + nh + (row_stats ? 3 * units : 0);
+      nh * d + R + units + 2 * nh + nh + (row_stats ? 3 * units : 0);
   float* small = static_cast<float*>(scratch(kScratchMisc, small_words * sizeof(float), stream, &st));
   if (!small) return st;
   t->hdiag = small;
   t->diag = t->hdiag + nh * d;
   t->uexp = reinterpret_cast<int*>(t->diag + R);
-  t->hpart = reinterpret_cast<float*>(t->uexp + units);
-  t->hexp = reinterpret_cast<int*>(t->hpart + nh * kAbsMaxBlocks);
+  t->hmax = reinterpret_cast<HMax*>(t->uexp + units);
+  t->hexp = reinterpret_cast<int*>(t->hmax + nh);
   t->rstats = row_stats ? reinterpret_cast<float*>(t->hexp + nh) : nullptr;
   t->D = static_cast<uint16_t*>(scratch(kScratchD, t->R_pad * d * 2, stream, &st));
   if (!t->D) return st;
@@ -755,18 +746,19 @@ bitsmoe_status loss_table_setup(int64_t d, int64_t R, int64_t units, bool row_st
 }
 
 // H -> scaled fp16 H_off and diag(H).  Bound by memory: 128 H of 2048 take
-// 274 us for the maximum and 425 us for H_off (404 and 550 when both went over
-// the whole square).  Taking a few H at a time through both, for the second
-// to find them in the last-level cache, was slower (368 and 369: the launches
-// are too short to run at full bandwidth).
+// 490 us in all, against 274 + 425 with a pass for max |H| first.
 bitsmoe_status loss_table_hoff(const float* H_dev, const LossTable& t, hipStream_t s, const char* who) {
   const int64_t blocks = hoff_blocks(t.tiles_m, t.d / gemm::kTileK);
   if (blocks > INT32_MAX) return fail(BITSMOE_ERR_SHAPE, std::string(who) + ": too many blocks");
   const unsigned nh = static_cast<unsigned>(t.nh);
-  hipLaunchKernelGGL(habsmax_kernel, dim3(kAbsMaxBlocks, nh), dim3(256), 0, s, H_dev, t.d, t.hpart);
+  hipLaunchKernelGGL(hdiagmax_kernel, dim3(nh), dim3(1024), 0, s, H_dev, t.d, t.hmax);
   BITSMOE_LAUNCH_CHECK(who);
   hipLaunchKernelGGL(hoff_kernel, dim3(static_cast<unsigned>(blocks), nh), dim3(256), 0, s, H_dev,
-                     t.d, t.d_pad, t.hpart, t.Hoff, t.hdiag, t.hexp);
+                     t.d, t.d_pad, t.hmax, t.Hoff, t.hdiag, t.hexp);
+  BITSMOE_LAUNCH_CHECK(who);
+  // (few workgroups: nearly always they return at once)
+  hipLaunchKernelGGL(hoff_redo_kernel, dim3(static_cast<unsigned>(std::min<int64_t>(blocks, nh > 8 ? 32 : 256)), nh),
+                     dim3(256), 0, s, H_dev, t.d, t.d_pad, t.hmax, blocks, t.Hoff, t.hdiag, t.hexp);
   BITSMOE_LAUNCH_CHECK(who);
   return BITSMOE_OK;
 }

@@ -136,6 +136,43 @@ def test_score_routed(E, upe, d, bits, group):
     assert np.array_equal(Lsh, Lr)
 
 
+@pytest.mark.parametrize("scale", [1.0, 1e-7, 3e6])
+def test_score_scale_of_matrices_without_a_dominant_diagonal(scale):
+    """H_off's scale is taken from the diagonal and checked against every
+    entry: symmetric matrices whose largest entry is off the diagonal (in the
+    first and the last block of the upper triangle), on it, or whose diagonal
+    is zero, next to each other.  Bound: fp16 rounding of both operands
+    (2^-11 each) relative to the sum of the magnitudes of all terms."""
+    say("score scale", scale)
+    g = np.random.default_rng(11)
+    d, upe, bits, group = 320, 64, (1, 2, 3, 4), 64
+    S = g.standard_normal((4, d, d))
+    S = (S + S.transpose(0, 2, 1)) / 2
+    S[0] = S[0] @ S[0].T / d
+    S[1, 0, 9] = S[1, 9, 0] = 70.0
+    S[2, 300, 319] = S[2, 319, 300] = -500.0
+    S[3][np.arange(d), np.arange(d)] = 0.0
+    Hs = (S * scale).astype(np.float32)
+    C = synth.random_rows(4 * upe, d, seed=5, scale=0.05, heavy=True)
+    L = bm.score_routed(dev(C, "f32"), dev(Hs, "f32"), upe, bits, group).cpu().numpy()
+    for e in range(4):
+        rows = C[e * upe:(e + 1) * upe]
+        H64 = Hs[e].astype(np.float64)
+        ref = oracle.score(rows, H64, bits, group)
+        mag = oracle.score(rows, np.abs(H64), bits, group)  # not below what cancels ...
+        err = np.abs(L[e * upe:(e + 1) * upe] - ref)
+        # ... but its own terms cancel too: the spread of the errors decides
+        den = np.maximum(np.abs(mag), np.linalg.norm(H64) * _err2(rows, bits, group))
+        assert np.all(err <= 2.0**-10 * den), (e, float(np.max(err / den)))
+        one = bm.score(dev(rows, "f32"), dev(Hs[e], "f32"), bits, group).cpu().numpy()
+        assert np.array_equal(one, L[e * upe:(e + 1) * upe])
+
+
+def _err2(rows, bits, group):
+    """|delta|^2 of every row and width: the loss under H = I."""
+    return oracle.score(rows, np.eye(rows.shape[1]), bits, group)
+
+
 def test_routed_qwen_gate_full_size_sampled():
     """The Qwen3-30B-A3B gate shape: 128 routed Grams of 2048^2, the loss table
     of 49152 units against them, sampled rows checked."""
