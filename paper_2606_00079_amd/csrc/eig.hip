@@ -8,7 +8,7 @@
 //
 //   1. Householder reduction to tridiagonal form, T = Q^T M Q: up to n = 2048
 //      in one launch with the matrix in registers (tridiag.hip: of one
-//      workgroup up to 192, of the whole device above), beyond in panels of
+//      workgroup up to 128, of the whole device above), beyond in panels of
 //      NB columns (the blocked scheme of LAPACK's symmetric reduction, lower
 //      form, stored by rows since M is symmetric).  Per column i of a panel:
 //        trsymv_kernel  the reflector H_i = I - tau v v^T that zeroes row i
@@ -625,7 +625,7 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t 
   hipError_t he;
   // 1. tridiagonal reduction: in one launch where the matrix fits the
   // register files (n <= 2048 on 256 compute units; 28.9 -> 6.4 ms at n =
-  // 2048; up to 192 those of one compute unit), else a panel at a time
+  // 2048; up to 128 those of one compute unit), else a panel at a time
   const bool one_cu = tridiag_small_fits(n);
   bool resident = !one_cu && tridiag_resident_fits(n);
   if (one_cu) {

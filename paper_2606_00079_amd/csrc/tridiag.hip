@@ -278,13 +278,13 @@ __global__ __launch_bounds__(kThreads) void tridiag_kernel(
 // wave's rows and the three fma per entry: TRI128 us at n = 128 (239 with
 // workgroups of eight rows), TRI192 at 192 (TRI192OLD).
 template <int W, int CPT>
-__global__ __launch_bounds__(64 * W) void tridiag_small_kernel(
+__global__ __launch_bounds__(64 * (W + 1)) void tridiag_small_kernel(
     const double* __restrict__ M, int n, double* __restrict__ V, double* __restrict__ dvec,
     double* __restrict__ evec, double* __restrict__ tau) {
   constexpr int RW = 64 * CPT / W;  // rows per wave
   constexpr int RG = 4;             // rows taken together
-  static_assert(64 % W == 0 && RW % RG == 0, "rows are dealt to the waves in turn");
-  __shared__ double s_q[2][W][64 * CPT], s_a[2][64 * CPT];
+  static_assert(64 % W == 0 && RW % RG == 0 && CPT <= 2, "rows are dealt to the waves in turn");
+  __shared__ double s_q[2][W][64 * CPT], s_a[2][64 * CPT], s_r[2][2];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   double A[RW][CPT], v[CPT], w[CPT], x[CPT];
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(64 * W) void tridiag_small_kernel(
 #pragma unroll
     for (int q = 0; q < RW; ++q) {
       const int r = wave + W * q;
-      A[q][k] = r < n && c < n ? M[static_cast<int64_t>(r) * n + c] : 0.0;
+      A[q][k] = wave < W && r < n && c < n ? M[static_cast<int64_t>(r) * n + c] : 0.0;
     }
   }
   // entry c of a vector over the columns, the same in every lane
@@ -309,65 +309,75 @@ __global__ __launch_bounds__(64 * W) void tridiag_small_kernel(
   double dcur = M[0];
   for (int i = 0; i + 1 < n; ++i) {
     const int par = i & 1;
-    const double alpha = entry(x, i + 1);
-    double xp[CPT], acc[CPT], sg = 0.0;
+    double xp[CPT], acc[CPT];
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
       xp[k] = lane + 64 * k > i + 1 ? x[k] : 0.0;
-      sg = fma(xp[k], xp[k], sg);
       acc[k] = 0.0;
     }
-    // the pending rank-2 update, A x' over this wave's rows, and row i + 1.
-    // Rows up to i and columns in blocks left of k0 are done: groups of rows
-    // are skipped whole, the others' values there are of no consequence
-    // (x', v and w are zero).
-    auto rows = [&]<int K0>() {
+    if (wave < W) {
+      // the pending rank-2 update, A x' over this wave's rows, and row i + 1.
+      // Rows up to i and columns in blocks left of k0 are done: groups of rows
+      // are skipped whole, the others' values there are of no consequence
+      // (x', v and w are zero).
+      auto rows = [&]<int K0>() {
 #pragma unroll
-      for (int g = 0; g < RW; g += RG) {
-        if (wave + W * (g + RG - 1) <= i) continue;  // uniform
+        for (int g = 0; g < RW; g += RG) {
+          if (wave + W * (g + RG - 1) <= i) continue;  // uniform
 #pragma unroll
-        for (int q = g; q < g + RG; ++q) {
-          const int kr = W * q / 64, lr = wave + W * q % 64;
-          const double vr = readlane_f64(v[kr], lr), wr = readlane_f64(w[kr], lr);
-          const double xr = readlane_f64(xp[kr], lr);
+          for (int q = g; q < g + RG; ++q) {
+            const int kr = W * q / 64, lr = wave + W * q % 64;
+            const double vr = readlane_f64(v[kr], lr), wr = readlane_f64(w[kr], lr);
+            const double xr = readlane_f64(xp[kr], lr);
 #pragma unroll
-          for (int k = K0; k < CPT; ++k) {
-            A[q][k] = fma(-vr, w[k], fma(-wr, v[k], A[q][k]));
-            acc[k] = fma(A[q][k], xr, acc[k]);
+            for (int k = K0; k < CPT; ++k) {
+              A[q][k] = fma(-vr, w[k], fma(-wr, v[k], A[q][k]));
+              acc[k] = fma(A[q][k], xr, acc[k]);
+            }
           }
+#pragma unroll
+          for (int q = g; q < g + RG; ++q)
+            if (wave + W * q == i + 1) {  // uniform
+#pragma unroll
+              for (int k = K0; k < CPT; ++k) s_a[par][lane + 64 * k] = A[q][k];
+            }
         }
-#pragma unroll
-        for (int q = g; q < g + RG; ++q)
-          if (wave + W * q == i + 1) {  // uniform
-#pragma unroll
-            for (int k = K0; k < CPT; ++k) s_a[par][lane + 64 * k] = A[q][k];
-          }
+      };
+      const int k0 = (i + 1) / 64;
+      if constexpr (CPT >= 2) {
+        if (k0 == 1) rows.template operator()<1>();
       }
-    };
-    const int k0 = (i + 1) / 64;
-    if constexpr (CPT >= 3) {
-      if (k0 == 2) rows.template operator()<2>();
-    }
-    if constexpr (CPT >= 2) {
-      if (k0 == 1) rows.template operator()<1>();
-    }
-    if (k0 == 0) rows.template operator()<0>();
+      if (k0 == 0) rows.template operator()<0>();
 #pragma unroll
-    for (int k = 0; k < CPT; ++k) s_q[par][wave][lane + 64 * k] = acc[k];
-    // the reflector of row i
-    const double sigma = wave_sum_dpp(sg);
-    double beta = alpha, t = 0.0, sc = 0.0;
-    if (sigma != 0.0) {
-      beta = -copysign(sqrt(fma(alpha, alpha, sigma)), alpha);
-      t = (beta - alpha) / beta;
-      sc = 1.0 / (alpha - beta);
+      for (int k = 0; k < CPT; ++k) s_q[par][wave][lane + 64 * k] = acc[k];
+    } else {
+      // the reflector of row i
+      const double alpha = entry(x, i + 1);
+      double sg = 0.0;
+#pragma unroll
+      for (int k = 0; k < CPT; ++k) sg = fma(xp[k], xp[k], sg);
+      const double sigma = wave_sum_dpp(sg);
+      double beta = alpha, t = 0.0, sc = 0.0;
+      if (sigma != 0.0) {
+        beta = -copysign(sqrt(fma(alpha, alpha, sigma)), alpha);
+        t = (beta - alpha) / beta;
+        sc = 1.0 / (alpha - beta);
+      }
+      if (lane == 0) {
+        s_r[par][0] = sc;
+        s_r[par][1] = t;
+        dvec[i] = dcur;
+        evec[i] = beta;
+        tau[i] = t;
+      }
     }
+    lds_barrier();
+    const double sc = s_r[par][0], t = s_r[par][1];
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
       const int c = lane + 64 * k;
       v[k] = c > i + 1 ? x[k] * sc : (c == i + 1 ? 1.0 : 0.0);
     }
-    lds_barrier();
     double p[CPT], a[CPT], sp = 0.0;
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
@@ -384,16 +394,11 @@ __global__ __launch_bounds__(64 * W) void tridiag_small_kernel(
 #pragma unroll
     for (int k = 0; k < CPT; ++k) w[k] = t * p[k] - K * v[k];
     const double w1 = entry(w, i + 1);
-    if (wave == i % W) {
+    if (wave == W) {
 #pragma unroll
       for (int k = 0; k < CPT; ++k) {
         const int c = lane + 64 * k;
         if (c < n) V[static_cast<int64_t>(i) * n + c] = v[k];
-      }
-      if (lane == 0) {
-        dvec[i] = dcur;
-        evec[i] = beta;
-        tau[i] = t;
       }
     }
     dcur = entry(a, i + 1) - 2.0 * w1;
@@ -409,20 +414,16 @@ __global__ __launch_bounds__(64 * W) void tridiag_small_kernel(
 
 }  // namespace
 
-bool tridiag_small_fits(int64_t n) { return n >= 2 && n <= 192; }
+bool tridiag_small_fits(int64_t n) { return n >= 2 && n <= 128; }
 
 void tridiag_small(const double* M, int64_t n64, double* V, double* dvec, double* evec, double* tau,
                    void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int n = static_cast<int>(n64);
-  // four waves while a wave's rows fit its registers (n = 128: 128 of 256
-  // beside the rest), eight beyond
   if (n <= 64)
-    hipLaunchKernelGGL((tridiag_small_kernel<4, 1>), dim3(1), dim3(256), 0, s, M, n, V, dvec, evec, tau);
-  else if (n <= 128)
-    hipLaunchKernelGGL((tridiag_small_kernel<4, 2>), dim3(1), dim3(256), 0, s, M, n, V, dvec, evec, tau);
+    hipLaunchKernelGGL((tridiag_small_kernel<4, 1>), dim3(1), dim3(320), 0, s, M, n, V, dvec, evec, tau);
   else
-    hipLaunchKernelGGL((tridiag_small_kernel<8, 3>), dim3(1), dim3(512), 0, s, M, n, V, dvec, evec, tau);
+    hipLaunchKernelGGL((tridiag_small_kernel<4, 2>), dim3(1), dim3(320), 0, s, M, n, V, dvec, evec, tau);
 }
 
 bool tridiag_resident_fits(int64_t n) {

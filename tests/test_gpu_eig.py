@@ -55,7 +55,7 @@ def _check_invariants(M, Ut, ev, r):
                                  (191, 20), (192, 192), (193, 30)])
 def test_reduction_by_one_workgroup_edges(n, r):
     """Sizes on both sides of each form of the one-workgroup reduction (64
-    columns per lane step, at most 192), with row and column counts that
+    columns per lane step, at most 128), with row and column counts that
     leave its last waves partly empty."""
     say("one workgroup", n, r)
     M = _separated(n, seed=3 * n + r)
