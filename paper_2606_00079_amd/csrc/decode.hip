@@ -1026,7 +1026,8 @@ __global__ __launch_bounds__(256) void zin_kernel(const float* __restrict__ Vt, 
 // Thread (slice rs, segment sg) owns the 16 outputs 16 sg .. 16 sg + 15 of
 // segment block blockIdx.x and the rows k = rs, rs + RSL, ... of the split;
 // a unit row's 16 entries there are half a word of each of its bit planes and
-// one group parameter, so c^ = q s + m is summed as (z s) q and z m.  The
+// one group parameter: c^ = q s + m in one fma (summing (z s) q and z m apart
+// saves that at one token and loses a bit to their cancellation).  The
 // RSL slices are added in slice order through LDS.
 //
 // The step is bound by its chains of loads (job, width and offset, planes),
@@ -1037,7 +1038,7 @@ __global__ __launch_bounds__(256) void zin_kernel(const float* __restrict__ Vt, 
 // that (32 with the prefetch took 312 and 52 us), the sums run over the
 // tokens the job has, slices are as many as the segments leave room for (SEGW
 // need not be a power of two), and the LDS rows of the reduction are padded to
-// 17 words (unpadded, all lanes of a store hit a few banks).  22.4 us there,
+// 17 words (unpadded, all lanes of a store hit a few banks).  23.4 us there,
 // against 28.5 with 32 outputs, four tokens always, and the loads in a row's
 // own iteration.
 constexpr int kInSeg = 16;  // outputs per thread
@@ -1068,13 +1069,11 @@ __global__ __launch_bounds__(256) void yin_kernel(
   const bool mine = rs < RSL && sg < nseg;
   // the job's first NT tokens
   auto body = [&]<int NT>() {
-    float acc[NT][kInSeg], macc[NT];
+    float acc[NT][kInSeg];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      macc[t] = 0.0f;
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int j = 0; j < kInSeg; ++j) acc[t][j] = 0.0f;
-    }
     // planes and parameter of the thread's row q of the staged ones
     struct Row {
       int b;
@@ -1132,13 +1131,9 @@ __global__ __launch_bounds__(256) void yin_kernel(
         } else if (cur.b != 0) {
           const float s = f16_bits_to_f32(static_cast<uint16_t>(cur.prm & 0xffffu));
           const float m = f16_bits_to_f32(static_cast<uint16_t>(cur.prm >> 16));
-          float zs[NT];
+          float zk[NT];
 #pragma unroll
-          for (int t = 0; t < NT; ++t) {
-            const float zk = s_z[t][q];
-            zs[t] = zk * s;
-            macc[t] = fmaf(zk, m, macc[t]);
-          }
+          for (int t = 0; t < NT; ++t) zk[t] = s_z[t][q];
           uint32_t qb[kInSeg / 4];
 #pragma unroll
           for (int kk = 0; kk < kInSeg / 4; ++kk) qb[kk] = spread4(cur.pw[0] >> (4 * kk));
@@ -1153,9 +1148,9 @@ __global__ __launch_bounds__(256) void yin_kernel(
           for (int kk = 0; kk < kInSeg / 4; ++kk)
 #pragma unroll
             for (int c4 = 0; c4 < 4; ++c4) {
-              const float qv = static_cast<float>((qb[kk] >> (8 * c4)) & 0xffu);
+              const float cv = fmaf(static_cast<float>((qb[kk] >> (8 * c4)) & 0xffu), s, m);
 #pragma unroll
-              for (int t = 0; t < NT; ++t) acc[t][4 * kk + c4] = fmaf(zs[t], qv, acc[t][4 * kk + c4]);
+              for (int t = 0; t < NT; ++t) acc[t][4 * kk + c4] = fmaf(zk[t], cv, acc[t][4 * kk + c4]);
             }
         }
         cur = nxt;
@@ -1168,7 +1163,7 @@ __global__ __launch_bounds__(256) void yin_kernel(
       __syncthreads();
       if (rs < RSL) {
 #pragma unroll
-        for (int j = 0; j < kInSeg; ++j) red[(rs * SEGW + sg_local) * kPad + j] = acc[t][j] + macc[t];
+        for (int j = 0; j < kInSeg; ++j) red[(rs * SEGW + sg_local) * kPad + j] = acc[t][j];
       }
       __syncthreads();
       const float wt = ew[i0 + t];
