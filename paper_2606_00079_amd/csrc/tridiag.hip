@@ -273,10 +273,15 @@ __global__ __launch_bounds__(kThreads) void tridiag_kernel(
 // it columns l, l + 64, ...  A x' is summed by columns (A is symmetric), so a
 // wave needs no sums over its lanes: each forms its rows' share of every
 // column, the shares meet in LDS, and after the one barrier of the column every
-// wave forms p, w and the next row for all columns by itself.  Two sets of
-// shares alternate.  Bound by the readlanes that spread x, v and w over a
-// wave's rows and the three fma per entry: TRI128 us at n = 128 (239 with
-// workgroups of eight rows), TRI192 at 192 (TRI192OLD).
+// wave forms p, w and the next row for all columns by itself.  One more wave
+// has no rows: it forms the reflector (a sum, a square root and two divisions
+// in series) while the others are at theirs.  Two sets of shares alternate.
+// Bound by the serial chain of a column (0.96 us at n = 64, where the rows are
+// few) and, from there on, the readlanes that spread x, v and w over a wave's
+// rows: 164 us at n = 128, against 239 with workgroups of eight rows.  Eight
+// waves are slower than four (209 us against 180, with the reflector in every
+// wave: what all waves do costs more than fewer rows save), and so is this
+// form beyond two columns a lane (2.9 us per column at 160).
 template <int W, int CPT>
 __global__ __launch_bounds__(64 * (W + 1)) void tridiag_small_kernel(
     const double* __restrict__ M, int n, double* __restrict__ V, double* __restrict__ dvec,
