@@ -134,6 +134,9 @@ struct Problem {
   // tiles of its next tile before the epilogue of the current one, so the
   // epilogue's stores overlap the next tile's loads.
   int64_t persist;
+  // with the kernel's ZK flag: batch z has koff[z + 1] - koff[z] valid K
+  // entries per segment (the rest of its operands is not read)
+  const int64_t* koff;
 };
 
 // Logical (XCD-contiguous) range of XCD x when n logical ids are spread as
@@ -560,9 +563,10 @@ __device__ __forceinline__ f16x8 bf16x8_to_f16x8(const uint32_t (&w)[4]) {
 // PERSIST: compiled for a persistent launch (Problem::persist > 0).
 // ONEK: compiled for a one-pass, one-segment problem without repeat_k (the
 // K walk is a fixed step per tile; persistent launches always are).
+// ZK: the K extent is the batch's own (Problem::koff; one tile per workgroup).
 template <int BM, int BN, int KB, int STAGES, class Epi, bool F16 = false, bool BKN = false,
           bool PAIRED = false, bool CVTB = false, bool PERSIST = false, bool ONEK = false,
-          int NWN = 2>
+          int NWN = 2, bool ZK = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_nt_kernel(Problem p, Epi epi) {
   static_assert(BM % 64 == 0 && BN % 64 == 0, "tile");
@@ -635,6 +639,11 @@ void gemm_nt_kernel(Problem p, Epi epi) {
   f.tm = tm0;
   f.tn = tn0;
 
+  if constexpr (ZK) {
+    static_assert(!PAIRED && !PERSIST, "one batch per workgroup");
+    p.kseg = uniform64((p.koff[f.z + 1] - p.koff[f.z] + KB - 1) / KB * KB);
+    p.ktiles = p.passes * p.segs * p.kseg / BK;
+  }
   const int64_t ktiles = p.ktiles * BK / KB;  // K tiles of this kernel's step
   int64_t kt0 = ktiles * f.ks / p.splits;
   int64_t kt1 = ktiles * (f.ks + 1) / p.splits;

@@ -97,6 +97,28 @@ def test_grams_without_split(d, dt):
     assert np.array_equal(Mi, Mi.T) and relfro(Mi, W64 @ W64.T) <= bar
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_gram_routed_own_token_counts(dt):
+    """Enough experts that K is not split: every expert's K ends with its own
+    tokens, from none over the edges of a K tile to several tiles."""
+    say("gram_routed own counts", dt)
+    g = np.random.default_rng(8)
+    E, n, d = 128, 300, 576
+    cnt = np.r_[0, 1, 31, 32, 33, 63, 64, 65, 200, g.integers(0, 40, E - 9)].astype(np.int64)
+    off = np.r_[0, np.cumsum(cnt)].astype(np.int64)
+    tok = g.integers(0, n, off[-1]).astype(np.int32)
+    w = g.random(off[-1]).astype(np.float32)
+    X = dev(synth.random_rows(n, d, seed=8, scale=1.0, heavy=True), "f32")
+    X = X if dt == "f32" else X.to(torch.bfloat16)
+    Hs = bm.gram_routed(X, off, tok, w).cpu().numpy()
+    ref = routed.gram_routed(X.double().cpu().numpy(), off, tok, w)
+    for e in range(E):
+        assert np.array_equal(Hs[e], Hs[e].T)
+        # as for the shared Gram, over up to 200 tokens
+        assert relfro(Hs[e], ref[e]) <= 2.0**-17 + 2.0**-18 + max(1, cnt[e]) * 2.0**-24, e
+    assert np.all(Hs[0] == 0.0)
+
+
 def test_gram_routed_empty_expert_and_ragged_rows():
     g = np.random.default_rng(3)
     X = synth.random_rows(150, 192, seed=3, scale=1.0, heavy=True)
