@@ -664,11 +664,16 @@ def main(argv=None) -> int:
     score_flops = sum(2.0 * p.E * p.r * len(p.bits) * p.spec.d_in ** 2 for p in layer)
 
     def score_executed(p):
-        # the kernel reads only the upper block triangle of the symmetric H
-        # (256 x 256 blocks): row tile t of H multiplies K = d - 256 t columns
+        # the kernel reads only the upper triangle of the symmetric H: row tile
+        # t (256 rows) multiplies the columns right of its diagonal block and,
+        # in that block, the 32 x 32 blocks at and right of the diagonal
         d = p.spec.d_in
         rows = math.ceil(p.E * p.r * len(p.bits) / 256) * 256
-        return sum(2.0 * rows * 256 * (d - 256 * t) for t in range(math.ceil(d / 256)))
+
+        def entries(t):
+            w = min(256, d - 256 * t)
+            return 256 * (d - 256 * t - w) + 1024 * (w // 32) * (w // 32 + 1) // 2
+        return sum(2.0 * rows * entries(t) for t in range(math.ceil(d / 256)))
     score_exec_flops = sum(score_executed(p) for p in layer)
     dgen_bytes = sum(p.E * p.r * p.spec.d_in * (4 + 2 * len(p.bits)) for p in layer)
     pack_bytes = sum(p.E * p.r * p.spec.d_in * 4 + p.budget_bits * p.spec.d_in / 8

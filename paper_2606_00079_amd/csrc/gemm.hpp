@@ -718,7 +718,10 @@ void gemm_nt_kernel(Problem p, Epi epi) {
     for (int q = 0; q < LPS; ++q) issue_part(is, q);
   };
 
-  const int arow = f.wm * F::WM + (f.lane & 31);
+  // PAIRED: the waves take the 32-row blocks of the tile in turn, so that each
+  // has its share of any K tile's rows up to its diagonal (`tile` below)
+  constexpr int kRowStep = PAIRED ? 32 * (4 / NWN) : 32;  // between a wave's row fragments
+  const int arow = f.wm * (PAIRED ? 32 : F::WM) + (f.lane & 31);
   const int brow = f.wn * F::WN + (f.lane & 31);
   const int jq = f.lane >> 5;
   // Two register sets of operand fragments: while the matrix cores work on
@@ -739,7 +742,7 @@ void gemm_nt_kernel(Problem p, Epi epi) {
     if constexpr (q == 0 || q > F::FN) {
       constexpr int mi = q == 0 ? 0 : q - F::FN;
       const uint16_t* la = As + s * ASZ;
-      fa[T][mi] = *reinterpret_cast<const typename Op::vec*>(&la[lds_off<KB>(arow + 32 * mi, j)]);
+      fa[T][mi] = *reinterpret_cast<const typename Op::vec*>(&la[lds_off<KB>(arow + kRowStep * mi, j)]);
     } else {
       constexpr int ni = q - 1;
       const uint16_t* lb = Bs + s * BSZ;
@@ -794,8 +797,13 @@ void gemm_nt_kernel(Problem p, Epi epi) {
   struct FragSrc {
     int s, kk;
   };
-  auto mfmas = [&](auto set, auto has_fr, auto lrange, const FragSrc& frs, const Issue& is) {
+  // TRI: only the first `rows` row fragments are multiplied (the others'
+  // part of A is zero in this K tile), by a test per op: a copy of the code
+  // for every number of rows ended in 300 spilled registers.
+  auto mfmas = [&](auto set, auto has_fr, auto lrange, const FragSrc& frs, const Issue& is, auto tri,
+                   int rows) {
     constexpr int T = decltype(set)::value;
+    constexpr bool TRI = decltype(tri)::value;
     using Other = std::integral_constant<int, 1 - T>;
     constexpr int L0 = decltype(lrange)::first, L1 = decltype(lrange)::second;
     constexpr int NF = decltype(has_fr)::value ? NFR : 0;
@@ -818,7 +826,7 @@ void gemm_nt_kernel(Problem p, Epi epi) {
     StaticFor<0, Q>::run([&](auto qq) {
       constexpr int q = decltype(qq)::value;
       constexpr int mi = q / F::FN, ni = q % F::FN;
-      f.acc[mi][ni] = Op::mfma(fa[T][mi], fb[T][ni], f.acc[mi][ni]);
+      if (!TRI || mi < rows) f.acc[mi][ni] = Op::mfma(fa[T][mi], fb[T][ni], f.acc[mi][ni]);
       // memory instructions j0 .. j1-1 of the alternating sequence F0, L0,
       // F1, L1, ... (the longer list continuing alone)
       constexpr int j0 = q < QS ? q * M / QS : M, j1 = q < QS ? (q + 1) * M / QS : M;
@@ -883,7 +891,13 @@ void gemm_nt_kernel(Problem p, Epi epi) {
   // K tile i (fragments of its first step already requested into set 0).
   // has_next: tile i + 1 exists; refill: tile i + STAGES - 1 exists (into
   // the buffer of tile i - 1, free since the barrier before this tile).
-  auto tile = [&](int64_t i, auto has_next, auto refill, auto tail) {
+  // tri (PAIRED, KB = 32): K tile i is one of the diagonal block, tile q = nk -
+  // 1 - i of it, which concerns the tile's rows up to 32 q + 31 only (A is
+  // zero below its 32-wide diagonal): of the BM / 32 row blocks, q + 1.
+  auto tile = [&](int64_t i, auto has_next, auto refill, auto tail, auto tri) {
+    constexpr int kWaveRows = 4 / NWN;  // waves that share the row blocks
+    const int rows = (static_cast<int>(nk - i) - f.wm + kWaveRows - 1) / kWaveRows;
+    using Tri = decltype(tri);
     const int s = static_cast<int>(i % STAGES);
     Issue is{};
     if constexpr (decltype(refill)::value) {
@@ -896,12 +910,12 @@ void gemm_nt_kernel(Problem p, Epi epi) {
       constexpr int la = decltype(refill)::value ? kk * LPS / KS : 0;
       constexpr int lb = decltype(refill)::value ? (kk + 1) * LPS / KS : 0;
       if constexpr (kk + 1 < KS) {
-        mfmas(Cur(), True(), LoadRange<la, lb>(), FragSrc{s, kk + 1}, is);
+        mfmas(Cur(), True(), LoadRange<la, lb>(), FragSrc{s, kk + 1}, is, Tri(), rows);
       } else if constexpr (decltype(has_next)::value) {
         sync_tile(i + 1, tail);
-        mfmas(Cur(), True(), LoadRange<la, lb>(), FragSrc{static_cast<int>((i + 1) % STAGES), 0}, is);
+        mfmas(Cur(), True(), LoadRange<la, lb>(), FragSrc{static_cast<int>((i + 1) % STAGES), 0}, is, Tri(), rows);
       } else {
-        mfmas(Cur(), False(), LoadRange<la, lb>(), FragSrc{0, 0}, is);
+        mfmas(Cur(), False(), LoadRange<la, lb>(), FragSrc{0, 0}, is, Tri(), rows);
       }
     });
   };
@@ -963,9 +977,18 @@ void gemm_nt_kernel(Problem p, Epi epi) {
       }
       read_frags(Set0(), 0, 0);
       int64_t i = 0;
-      for (; i + STAGES - 1 < nk; ++i) tile(i, True(), True(), False());
-      for (; i + 1 < nk; ++i) tile(i, True(), False(), True());
-      tile(i, False(), False(), True());
+      if constexpr (PAIRED && KB == 32) {
+        // the last BM / KB tiles are the diagonal block's
+        static_assert(BM / KB >= STAGES - 1, "the tiles without a refill are in the diagonal block");
+        for (; i + BM / KB < nk; ++i) tile(i, True(), True(), False(), False());
+        for (; i + STAGES - 1 < nk; ++i) tile(i, True(), True(), False(), True());
+        for (; i + 1 < nk; ++i) tile(i, True(), False(), True(), True());
+        tile(i, False(), False(), True(), True());
+      } else {
+        for (; i + STAGES - 1 < nk; ++i) tile(i, True(), True(), False(), False());
+        for (; i + 1 < nk; ++i) tile(i, True(), False(), True(), False());
+        tile(i, False(), False(), True(), False());
+      }
     }
     // Pin the accumulators to AGPRs across the loop: otherwise an epilogue
     // that feeds them to VALU instructions can pull part of them into VGPRs,

@@ -19,9 +19,9 @@
 //   2. dgen_kernel   one wave per unit: max |c_u|, group min/max, fake-quant
 //                    at every width, scaled fp16 error rows D[u*nb + j][:] and
 //                    the diagonal term of each (u, j)
-//   3. gemm          acc[i][row] = sum_k H'[i][k] D[row][k] over the k blocks at
-//                    and right of i's block (H' = H_off there, doubled right of
-//                    the diagonal block: H is symmetric), epilogue
+//   3. gemm          acc[i][row] = sum_k H'[i][k] D[row][k] over the 32-wide k
+//                    blocks at and right of i's block (H' = H_off there, doubled
+//                    right of the diagonal block: H is symmetric), epilogue
 //                    sum_i D[row][i] acc[i][row] per 256-wide i tile
 //   4. finalize      L = diagonal term + the unscaled tile partials, in a fixed
 //                    order.
@@ -82,10 +82,11 @@ __global__ __launch_bounds__(1024) void hdiagmax_kernel(const float* __restrict_
 
 // H -> fp16 H_off * 2^F (zero diagonal) in the K-tiled layout of 256-row
 // tiles (rows padded to a multiple of 256 with zeros), and fp32 diag(H).
-// H is symmetric and the GEMM reads only the upper block triangle: row tile
-// t uses column blocks t (weight 1) and t + 1, ... (weight 2, which stands
-// for the mirrored lower blocks); blocks left of the diagonal are neither
-// read nor written.  `bx` counts the 256 x 32 blocks of the layout.
+// H is symmetric and the GEMM reads only the upper triangle of 32 x 32 blocks:
+// row block t uses column blocks t (weight 1) and t + 1, ... (weight 2, which
+// stands for the mirrored lower blocks).  Blocks left of a row tile's 256-wide
+// diagonal block are neither read nor written, those left of the 32-wide
+// diagonal inside it are zero (the GEMM leaves them out).  `bx` counts the 256 x 32 blocks of the layout.
 // Number of blocks at and right of the diagonal of row tiles 0 .. rt - 1.
 __host__ __device__ __forceinline__ int64_t hoff_blocks(int64_t rt, int64_t nkt) {
   constexpr int64_t per = SBM / gemm::kTileK;
@@ -113,7 +114,6 @@ __device__ __forceinline__ float hoff_block(const float* __restrict__ H, int64_t
       h[x][q] = v.x; h[x][q + 1] = v.y; h[x][q + 2] = v.z; h[x][q + 3] = v.w;
     }
   }
-  const int e = kt / (SBM / gemm::kTileK) > rt ? F + 1 : F;
   uint16_t* dst = Hoff + (rt * nkt + kt) * TB;
   float m = 0.0f;
 #pragma unroll
@@ -121,11 +121,13 @@ __device__ __forceinline__ float hoff_block(const float* __restrict__ H, int64_t
     const int w = 8 * (static_cast<int>(threadIdx.x) + 256 * x);
     const int64_t i = rt * SBM + w / gemm::kTileK;
     const int64_t k = kt * gemm::kTileK + w % gemm::kTileK;
+    const int64_t it = i / gemm::kTileK;  // K tile of the row's own diagonal entry
+    const int e = kt > it ? F + 1 : F;
     uint16_t v[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       m = fmaxf(m, fabsf(h[x][q]));
-      v[q] = f32_to_f16_bits(ldexpf(h[x][q], e));
+      v[q] = kt < it ? 0 : f32_to_f16_bits(ldexpf(h[x][q], e));
       if (i == k + q) {
         if (i < d) hdiag[i] = h[x][q];
         v[q] = 0;
@@ -435,9 +437,9 @@ __global__ __launch_bounds__(256) void dgen_kernel(const float* __restrict__ C, 
 //
 // The i range of the tile is K tiles 8 tm .. 8 tm + 7 of D (the diagonal
 // block), which the K loop visits last, in descending order: the first four
-// (the i range of the waves with wm = 0) are the last four tiles staged and
-// are still in the B halves of the stage buffers; the other four (wm = 1)
-// are loaded again into the A halves, which are free once the loop is done.
+// are the last four tiles staged and are still in the B halves of the stage
+// buffers; the other four are loaded again into the A halves, which are free
+// once the loop is done.  Row fragment mi of a wave is row block 2 mi + wm.
 // Both use the stage layout (256 rows x 32 entries, swizzled 16-byte
 // chunks).  Each lane then reads its D values (one row per column fragment,
 // four 8-byte runs per row fragment).  K tiles past the end of the row are
@@ -486,7 +488,7 @@ struct RowDot {
       float acc = 0.0f;
 #pragma unroll
       for (int mi = 0; mi < F::FM; ++mi) {
-        const int rq = 4 * f.wm + mi;  // block K tile (uniform per wave)
+        const int rq = 2 * mi + f.wm;  // row block = block K tile (uniform per wave)
         // rq < 4: staged as visit n = nk - 1 - rq, still in B buffer n % stages
         const int64_t n = lds.nk - 1 - rq;
         const uint16_t* tb = rq < 4 ? lds.b + static_cast<int>((n < 0 ? 0 : n) % lds.stages) * TE

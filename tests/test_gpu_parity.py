@@ -301,6 +301,32 @@ def test_score_deterministic_and_degenerate_rows():
     assert l_rel(a[3:], ref[3:]) <= REL
 
 
+@pytest.mark.parametrize("d", [64, 128, 192, 256, 320, 448, 512, 576, 768, 1088])
+def test_score_triangle_edges(d):
+    """Diagonal blocks of two to eight 32-wide K tiles, alone, last, and among
+    one to five row tiles: every entry of H counts once whatever its place
+    (H has large entries in single places of all kinds).  Bound: fp16 rounding
+    of both operands (2^-11 each) against the sum of the terms' magnitudes."""
+    say("score triangle", d)
+    g = np.random.default_rng(d)
+    H = g.standard_normal((d, d)) * 1e-3
+    H[np.arange(d), np.arange(d)] = 1.0
+    for i in range(0, d, 29):  # one strong coupling per row of a sample
+        k = int(g.integers(0, d))
+        H[i, k] = 5.0 * (1 if i % 2 else -1)
+    H = ((H + H.T) / 2).astype(np.float32)
+    C = synth.random_rows(130, d, seed=d, scale=0.05, heavy=True)
+    bits = [1, 2, 3]
+    L = bm.score(dev(C, "f32"), dev(H, "f32"), bits, 64).cpu().numpy()
+    H64 = H.astype(np.float64)
+    ref = oracle.score(C, H64, bits, 64)
+    rows = C.astype(np.float64)
+    for j, b in enumerate(bits):
+        delta = np.abs(rows - oracle.fake_quant(C, b, 64))
+        mag = np.einsum("ui,ik,uk->u", delta, np.abs(H64), delta, optimize=True)
+        assert np.all(np.abs(L[:, j] - ref[:, j]) <= 2.0**-10 * mag), (d, b)
+
+
 # ---------------------------------------------------------------------- pack
 @pytest.mark.parametrize("group,d,units", [(64, 256, 300), (128, 2048, 97), (32, 192, 65),
                                            (256, 768, 40), (128, 768, 90), (32, 1280, 33)])
