@@ -14,7 +14,7 @@
 // are scaled back by 2^-(2 E_u + F).  (bf16 operands, 8-bit precision, leave
 // per-entry errors close to 1e-3 on strongly correlated H; fp16 keeps them
 // near 1e-4 at the same matrix-core rate.)
-//   1. hdiagmax_kernel, hoff_kernel, hoff_redo_kernel
+//   1. habsmax_kernel or hdiagmax_kernel, hoff_kernel[, hoff_redo_kernel]
 //                    H -> scaled fp16 H_off (zero diagonal), fp32 diag(H)
 //   2. dgen_kernel   one wave per unit: max |c_u|, group min/max, fake-quant
 //                    at every width, scaled fp16 error rows D[u*nb + j][:] and
@@ -43,6 +43,7 @@ constexpr int SKB = 32;   // K step of the loss-table GEMM
 constexpr int SSTAGES = 4;  // LDS stages (two K tiles in flight)
 using gemm::BK;
 
+constexpr int kAbsMaxBlocks = 256;  // partial maxima of |H|
 constexpr int kF16Top = 14;         // scaled fp16 operands stay below 2^14
 
 // Exponent e with 0 <= v < 2^e (v finite, >= 0); 0 for v == 0.
@@ -54,11 +55,12 @@ __device__ __forceinline__ int exponent_above(float v) {
 
 // The scale 2^F of H_off comes from max |H|: F = kF16Top - 1 - e(max |H|), so
 // that doubled entries stay below 2^14.  The largest entry of a Gram is on its
-// diagonal, so hdiagmax_kernel looks there only, hoff_kernel converts with
-// that F and checks every entry it reads against the bound 2^e, and
+// diagonal, so for large inputs hdiagmax_kernel looks there only, hoff_kernel converts
+// with that F and checks every entry it reads against the bound 2^e, and
 // hoff_redo_kernel does the matrices again whose check failed (symmetric but not
-// semidefinite) with the maximum over the upper block triangle.  F is that of
-// the whole matrix in every case.
+// semidefinite) with the maximum over the upper block triangle.  Small inputs
+// (see loss_table_hoff) take the maximum over the triangle first: two launches
+// instead of three.  F is that of the whole matrix in every case.
 struct HMax {
   float diag;         // max |H_ii|
   uint32_t above;     // bits of the largest |H_ik| at or above the bound, 0: none
@@ -78,6 +80,46 @@ __global__ __launch_bounds__(1024) void hdiagmax_kernel(const float* __restrict_
     for (int w = 1; w < 16; ++w) m = fmaxf(m, red[w]);
     hmax[blockIdx.x] = HMax{m, 0u};
   }
+}
+
+// Partial maxima of |H_ik| over the upper block triangle (H is symmetric: a
+// bound for the off-diagonal maximum), one per block.  Row i counts from
+// its diagonal block on, columns 256 (i / 256) .. d - 1, so a wave takes
+// rows w and d - 1 - w: about the same number of entries for every wave.
+__global__ __launch_bounds__(256) void habsmax_kernel(const float* __restrict__ H, int64_t d,
+                                                      float* __restrict__ partial) {
+  __shared__ float red[4];
+  H += static_cast<int64_t>(blockIdx.y) * d * d;  // one H per blockIdx.y
+  partial += static_cast<int64_t>(blockIdx.y) * kAbsMaxBlocks;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  float m = 0.0f;
+  auto row_max = [&](int64_t i) {
+    const float* row = H + i * d;
+    // eight 16-byte loads in flight per lane
+    for (int64_t k0 = i / SBM * SBM; k0 < d; k0 += 8 * 256) {
+      float4 v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int64_t k = k0 + 256 * q + 4 * lane;
+        v[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (k < d) v[q] = *reinterpret_cast<const float4*>(row + k);
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        m = fmaxf(m, fmaxf(fmaxf(fabsf(v[q].x), fabsf(v[q].y)), fmaxf(fabsf(v[q].z), fabsf(v[q].w))));
+    }
+  };
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * 4;
+  for (int64_t w = static_cast<int64_t>(blockIdx.x) * 4 + wave; w < (d + 1) / 2; w += stride) {
+    row_max(w);
+    row_max(d - 1 - w);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  if (lane == 0) red[wave] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) partial[blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
 // H -> fp16 H_off * 2^F (zero diagonal) in the K-tiled layout of 256-row
@@ -142,19 +184,32 @@ __device__ __forceinline__ float hoff_block(const float* __restrict__ H, int64_t
   }
   return m;
 }
+// CHECK: F from the diagonal, checked; else from the maxima of habsmax_kernel.
+template <bool CHECK>
 __global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, int64_t d,
                                                    int64_t d_pad, HMax* __restrict__ hmax,
+                                                   const float* __restrict__ partial,
                                                    uint16_t* __restrict__ Hoff,
                                                    float* __restrict__ hdiag, int* __restrict__ hexp) {
   const int64_t z = blockIdx.y;  // one H per blockIdx.y
-  const float dm = hmax[z].diag;
-  const int e = exponent_above(dm);
+  float top;                     // the maximum that F comes from
+  if constexpr (CHECK) {
+    top = hmax[z].diag;
+  } else {
+    top = 0.0f;
+    for (int b = threadIdx.x & 63; b < kAbsMaxBlocks; b += 64) top = fmaxf(top, partial[z * kAbsMaxBlocks + b]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o, 64));
+  }
+  const int e = exponent_above(top);
   const int F = kF16Top - 1 - e;
   if (blockIdx.x == 0 && threadIdx.x == 0) hexp[z] = F;
   const float m = hoff_block(H + z * d * d, d, blockIdx.x, F, Hoff + z * d_pad * d, hdiag + z * d);
-  // (a zero diagonal bounds nothing: any entry has to be looked at)
-  const float bound = dm > 0.0f ? ldexpf(1.0f, e) : 0.0f;
-  if (m >= bound && m > 0.0f) atomicMax(&hmax[z].above, __float_as_uint(m));
+  if constexpr (CHECK) {
+    // (a zero diagonal bounds nothing: any entry has to be looked at)
+    const float bound = top > 0.0f ? ldexpf(1.0f, e) : 0.0f;
+    if (m >= bound && m > 0.0f) atomicMax(&hmax[z].above, __float_as_uint(m));
+  }
 }
 __global__ __launch_bounds__(256) void hoff_redo_kernel(const float* __restrict__ H, int64_t d,
                                                         int64_t d_pad, const HMax* __restrict__ hmax,
@@ -706,6 +761,7 @@ struct LossTable {
   float* diag;   // [R]
   int* uexp;     // [units]
   HMax* hmax;    // [nh]
+  float* hpart;  // [nh][kAbsMaxBlocks]
   int* hexp;     // [nh]
   float* rstats; // [3 units] (surrogate only)
   float* part;   // [R][tiles_m]
@@ -728,17 +784,18 @@ bitsmoe_status loss_table_setup(int64_t d, int64_t R, int64_t units, bool row_st
   t->Hoff = static_cast<uint16_t*>(scratch(kScratchA, nh * t->d_pad * d * 2, stream, &st));
   if (!t->Hoff) return st;
   // small tables: diag(H) [nh][d], diagonal terms [R], unit exponents
-  // [units], maxima of |H| [nh], the H_off exponents [nh], row statistics
-  // [3 units]
+  // [units], maxima of |H| [nh] and [nh][kAbsMaxBlocks], the H_off exponents
+  // [nh], row statistics [3 units]
   const int64_t small_words =
-      nh * d + R + units + 2 * nh + nh + (row_stats ? 3 * units : 0);
+      nh * d + R + units + (2 + kAbsMaxBlocks) * nh + nh + (row_stats ? 3 * units : 0);
   float* small = static_cast<float*>(scratch(kScratchMisc, small_words * sizeof(float), stream, &st));
   if (!small) return st;
   t->hdiag = small;
   t->diag = t->hdiag + nh * d;
   t->uexp = reinterpret_cast<int*>(t->diag + R);
   t->hmax = reinterpret_cast<HMax*>(t->uexp + units);
-  t->hexp = reinterpret_cast<int*>(t->hmax + nh);
+  t->hpart = reinterpret_cast<float*>(t->hmax + nh);
+  t->hexp = reinterpret_cast<int*>(t->hpart + nh * kAbsMaxBlocks);
   t->rstats = row_stats ? reinterpret_cast<float*>(t->hexp + nh) : nullptr;
   t->D = static_cast<uint16_t*>(scratch(kScratchD, t->R_pad * d * 2, stream, &st));
   if (!t->D) return st;
@@ -753,10 +810,22 @@ bitsmoe_status loss_table_hoff(const float* H_dev, const LossTable& t, hipStream
   const int64_t blocks = hoff_blocks(t.tiles_m, t.d / gemm::kTileK);
   if (blocks > INT32_MAX) return fail(BITSMOE_ERR_SHAPE, std::string(who) + ": too many blocks");
   const unsigned nh = static_cast<unsigned>(t.nh);
+  const dim3 grid(static_cast<unsigned>(blocks), nh);
+  // Up to 16 MB of H (one of 2048) the pass for the maximum takes about as long as
+  // the two launches that replace it (4.5 us), and a call of small sizes is
+  // bound by its launches (2 us each).
+  if (static_cast<double>(t.nh) * static_cast<double>(t.d) * static_cast<double>(t.d) <= double(1 << 22)) {
+    hipLaunchKernelGGL(habsmax_kernel, dim3(kAbsMaxBlocks, nh), dim3(256), 0, s, H_dev, t.d, t.hpart);
+    BITSMOE_LAUNCH_CHECK(who);
+    hipLaunchKernelGGL(hoff_kernel<false>, grid, dim3(256), 0, s, H_dev, t.d, t.d_pad, t.hmax, t.hpart,
+                       t.Hoff, t.hdiag, t.hexp);
+    BITSMOE_LAUNCH_CHECK(who);
+    return BITSMOE_OK;
+  }
   hipLaunchKernelGGL(hdiagmax_kernel, dim3(nh), dim3(1024), 0, s, H_dev, t.d, t.hmax);
   BITSMOE_LAUNCH_CHECK(who);
-  hipLaunchKernelGGL(hoff_kernel, dim3(static_cast<unsigned>(blocks), nh), dim3(256), 0, s, H_dev,
-                     t.d, t.d_pad, t.hmax, t.Hoff, t.hdiag, t.hexp);
+  hipLaunchKernelGGL(hoff_kernel<true>, grid, dim3(256), 0, s, H_dev, t.d, t.d_pad, t.hmax, t.hpart,
+                     t.Hoff, t.hdiag, t.hexp);
   BITSMOE_LAUNCH_CHECK(who);
   // (few workgroups: nearly always they return at once)
   hipLaunchKernelGGL(hoff_redo_kernel, dim3(static_cast<unsigned>(std::min<int64_t>(blocks, nh > 8 ? 32 : 256)), nh),

@@ -188,6 +188,12 @@ def test_score_scale_of_matrices_without_a_dominant_diagonal(scale):
         assert np.all(err <= 2.0**-10 * den), (e, float(np.max(err / den)))
         one = bm.score(dev(rows, "f32"), dev(Hs[e], "f32"), bits, group).cpu().numpy()
         assert np.array_equal(one, L[e * upe:(e + 1) * upe])
+    # enough matrices (44 of 320) that the scale comes from the diagonals: the
+    # same bits as from the pass over all entries
+    n = 11
+    many = bm.score_routed(dev(np.tile(C, (n, 1)), "f32"), dev(np.tile(Hs, (n, 1, 1)), "f32"), upe, bits,
+                           group).cpu().numpy()
+    assert np.array_equal(many, np.tile(L, (n, 1)))
 
 
 def _err2(rows, bits, group):
