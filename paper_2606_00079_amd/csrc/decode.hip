@@ -1325,32 +1325,41 @@ bitsmoe_status build_routing(const std::string& who, int64_t E, int64_t B,
   return ok();
 }
 
-// Device copies of the jobs [njobs][8], the weights [nnz] and the token entry
-// lists [B][kmax] in the small-table scratch; waits for the stream (the host
-// tables may go away after the call returns).
-bitsmoe_status upload_routing(const std::string& who, const RoutingTables& rt,
-                              const float* weights_host, int64_t B, void* stream, int4** jobs_d,
-                              int64_t** pidx_d, float** w_d) {
-  bitsmoe_status st;
-  const size_t job_bytes = static_cast<size_t>(std::max<int64_t>(rt.njobs, 1)) * 32;
-  const size_t pidx_bytes = static_cast<size_t>(B * rt.kmax) * 8;
-  const size_t w_bytes = (static_cast<size_t>(rt.nnz) * 4 + 15) / 16 * 16;
-  char* tab = static_cast<char*>(scratch(kScratchMisc, job_bytes + pidx_bytes + w_bytes + 64, stream, &st));
-  if (!tab) return st;
-  *jobs_d = reinterpret_cast<int4*>(tab);
-  *pidx_d = reinterpret_cast<int64_t*>(tab + job_bytes);
-  *w_d = reinterpret_cast<float*>(tab + job_bytes + pidx_bytes);
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  // one copy for the three tables
-  std::vector<char> host(job_bytes + pidx_bytes + w_bytes, 0);
-  if (rt.njobs > 0) std::memcpy(host.data(), rt.jobs.data(), static_cast<size_t>(rt.njobs) * 32);
-  std::memcpy(host.data() + job_bytes, rt.pidx.data(), pidx_bytes);
-  if (rt.nnz > 0) std::memcpy(host.data() + job_bytes + pidx_bytes, weights_host, static_cast<size_t>(rt.nnz) * 4);
-  hipError_t he = hipMemcpyAsync(tab, host.data(), host.size(), hipMemcpyHostToDevice, s);
-  if (he == hipSuccess) he = hipStreamSynchronize(s);
-  if (he != hipSuccess) return device_error((who + ": routing table copy").c_str(), he);
-  return ok();
-}
+// Device copies of the jobs [njobs][8], the token entry lists [B][kmax] and the
+// weights [nnz] in the small-table scratch, brought there by one copy.  `prepare`
+// does what can fail for want of memory, `copy` enqueues the copy and waits for
+// the stream (the host tables may go away after the call returns).
+struct RoutingUpload {
+  std::vector<char> host;
+  char* tab = nullptr;
+  int4* jobs = nullptr;
+  int64_t* pidx = nullptr;
+  float* w = nullptr;
+  bitsmoe_status prepare(const RoutingTables& rt, const float* weights_host, int64_t B, void* stream) {
+    const size_t job_bytes = static_cast<size_t>(std::max<int64_t>(rt.njobs, 1)) * 32;
+    const size_t pidx_bytes = static_cast<size_t>(B * rt.kmax) * 8;
+    const size_t w_bytes = (static_cast<size_t>(rt.nnz) * 4 + 15) / 16 * 16;
+    bitsmoe_status st;
+    tab = static_cast<char*>(scratch(kScratchMisc, job_bytes + pidx_bytes + w_bytes + 64, stream, &st));
+    if (!tab) return st;
+    jobs = reinterpret_cast<int4*>(tab);
+    pidx = reinterpret_cast<int64_t*>(tab + job_bytes);
+    w = reinterpret_cast<float*>(tab + job_bytes + pidx_bytes);
+    host.assign(job_bytes + pidx_bytes + w_bytes, 0);
+    if (rt.njobs > 0) std::memcpy(host.data(), rt.jobs.data(), static_cast<size_t>(rt.njobs) * 32);
+    std::memcpy(host.data() + job_bytes, rt.pidx.data(), pidx_bytes);
+    if (rt.nnz > 0)
+      std::memcpy(host.data() + job_bytes + pidx_bytes, weights_host, static_cast<size_t>(rt.nnz) * 4);
+    return BITSMOE_OK;
+  }
+  bitsmoe_status copy(const std::string& who, void* stream) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    hipError_t he = hipMemcpyAsync(tab, host.data(), host.size(), hipMemcpyHostToDevice, s);
+    if (he == hipSuccess) he = hipStreamSynchronize(s);
+    if (he != hipSuccess) return device_error((who + ": routing table copy").c_str(), he);
+    return ok();
+  }
+};
 
 // Launch shape of both kernels.
 struct DecodeGeom {
@@ -1674,17 +1683,16 @@ extern "C" bitsmoe_status bitsmoe_moe_decode(const uint64_t* codes_dev, const ui
                       static_cast<int>(rt.kmax), Y_dev, stream);
   }
   const DecodeGeom g = decode_geometry(rt.njobs, r, d_in, B);
-  int4* jobs_d;
-  int64_t* pidx_d;
-  float* w_d;
-  st = upload_routing("moe_decode", rt, weights_host, B, stream, &jobs_d, &pidx_d, &w_d);
+  RoutingUpload up;
+  st = up.prepare(rt, weights_host, B, stream);
+  if (st == BITSMOE_OK) st = up.copy("moe_decode", stream);
   if (st != BITSMOE_OK) return st;
   // partials zp [nnz][r]
   float* zp = static_cast<float*>(scratch(kScratchPart, std::max<int64_t>(rt.nnz, 1) * r * 4, stream, &st));
   if (!zp) return st;
   return decode_launch(g, rt.T, false, rt.njobs, codes_dev, params_dev, bits_dev, word_offsets_dev,
-                       total_words, E, r, d_in, group, Ut_dev, d_out, X_dev, B, jobs_d, nullptr, 1,
-                       w_d, pidx_d, static_cast<int>(rt.kmax), zp, Y_dev,
+                       total_words, E, r, d_in, group, Ut_dev, d_out, X_dev, B, up.jobs, nullptr, 1,
+                       up.w, up.pidx, static_cast<int>(rt.kmax), zp, Y_dev,
                        static_cast<hipStream_t>(stream));
 }
 
@@ -1790,17 +1798,23 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
   if (st != BITSMOE_OK) return st;
   // segments of 16 outputs: SEGW per workgroup (up to 256), RSL = 256 / SEGW
   // row slices; rows split over blockIdx.z for about 1024 workgroups but at
-  // least four rows per thread (each split adds a partial per output to the
-  // final sum; half as many splits moved 3 us from the sum to the rows)
+  // least four rows per thread and 32 in all (each split adds a partial per
+  // output to the final sum: at 23 tokens of a 384 x 768 projection half as many
+  // splits moved 3 us from the sum to the rows, at one token 20 splits of 20
+  // rows took 41.9 us where 12 of 32 take 40.5)
   const int64_t nseg = d_out / kInSeg;
   const int SEGW = static_cast<int>(std::min<int64_t>(nseg, 256));
   const int RSL = 256 / SEGW;
   const int64_t segblocks = (nseg + SEGW - 1) / SEGW;
+  const int64_t min_rows = std::max(4 * RSL, 32);
   int64_t nsplit = std::clamp<int64_t>(1024 / std::max<int64_t>(rt.njobs * segblocks, 1), 1,
-                                       std::max<int64_t>(1, (r + 4 * RSL - 1) / (4 * RSL)));
+                                       (r + min_rows - 1) / min_rows);
   const int64_t rows_split = (r + nsplit - 1) / nsplit;
   nsplit = (r + rows_split - 1) / rows_split;
   if (nsplit > 65535 || segblocks > 65535) return fail(BITSMOE_ERR_SHAPE, "moe_decode_in: too large");
+  RoutingUpload up;
+  st = up.prepare(rt, weights_host, B, stream);
+  if (st != BITSMOE_OK) return st;
   // z [B][r], partials yp [nsplit][nnz][d_out]
   const size_t zbytes = (static_cast<size_t>(B * r) * 4 + 255) / 256 * 256;
   char* part = static_cast<char*>(scratch(
@@ -1821,10 +1835,7 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
   }
   BITSMOE_LAUNCH_CHECK("moe_decode_in: z launch");
   // the basis product runs while the host copies the routing tables
-  int4* jobs_d;
-  int64_t* pidx_d;
-  float* w_d;
-  st = upload_routing("moe_decode_in", rt, weights_host, B, stream, &jobs_d, &pidx_d, &w_d);
+  st = up.copy("moe_decode_in", stream);
   if (st != BITSMOE_OK) return st;
   const uint32_t* pr = reinterpret_cast<const uint32_t*>(params_dev);
   const uint32_t* c32 = reinterpret_cast<const uint32_t*>(codes_dev);
@@ -1835,7 +1846,7 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
 #define BITSMOE_DECIN(TT)                                                                           \
   hipLaunchKernelGGL(yin_kernel<TT>, grid, dim3(256), 0, s, c32, pr, bits_dev, word_offsets_dev,    \
                      total_words, static_cast<int>(r), static_cast<int>(d_out), __builtin_ctz(group), SEGW, \
-                     static_cast<int>(rows_split), z, jobs_d, w_d, rt.nnz, yp)
+                     static_cast<int>(rows_split), z, up.jobs, up.w, rt.nnz, yp)
     if (rt.T == 4) BITSMOE_DECIN(4); else if (rt.T == 2) BITSMOE_DECIN(2); else BITSMOE_DECIN(1);
 #undef BITSMOE_DECIN
   }
@@ -1843,7 +1854,7 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
   {
     KernelTimer timer("moe_decode_in_sum", stream);
     hipLaunchKernelGGL(ysum_kernel, dim3(static_cast<unsigned>((d_out + 63) / 64), static_cast<unsigned>(B)),
-                       dim3(256), 0, s, yp, static_cast<int>(nsplit), rt.nnz, pidx_d,
+                       dim3(256), 0, s, yp, static_cast<int>(nsplit), rt.nnz, up.pidx,
                        static_cast<int>(rt.kmax), d_out, B, Y_dev);
   }
   BITSMOE_LAUNCH_CHECK("moe_decode_in: sum launch");
