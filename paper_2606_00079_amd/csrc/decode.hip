@@ -1033,7 +1033,8 @@ __global__ __launch_bounds__(256) void zin_kernel(const float* __restrict__ Vt, 
 // The step is bound by its chains of loads (job, width and offset, planes),
 // not by bytes (7.5 MB at 23 tokens of a 384 x 768 projection): the rows'
 // descriptors and z are staged in LDS for up to 256 rows at once, and the
-// planes of a thread's next row are loaded while the current one is summed.
+// planes of a thread's next row are loaded while the current one is summed
+// (for up to two tokens).
 // Sixteen outputs a thread leave registers for several waves per SIMD beside
 // that (32 with the prefetch took 312 and 52 us), the sums run over the
 // tokens the job has, slices are as many as the segments leave room for (SEGW
@@ -1109,10 +1110,13 @@ __global__ __launch_bounds__(256) void yin_kernel(
       }
       __syncthreads();
       Row cur, nxt;
-      fetch(kc, n, rs, cur);
+      if (NT < 4) fetch(kc, n, rs, cur);
       for (int q0 = 0; q0 < n; q0 += RSL) {
         const int q = q0 + rs;
-        fetch(kc, n, q + RSL, nxt);
+        if (NT < 4)
+          fetch(kc, n, q + RSL, nxt);
+        else
+          fetch(kc, n, q, cur);
         if (cur.b == 16) {
           const uint2* h = reinterpret_cast<const uint2*>(codes32 + 2 * s_o[q]) + 4 * sg;
 #pragma unroll
@@ -1153,7 +1157,7 @@ __global__ __launch_bounds__(256) void yin_kernel(
               for (int t = 0; t < NT; ++t) acc[t][4 * kk + c4] = fmaf(zk[t], cv, acc[t][4 * kk + c4]);
             }
         }
-        cur = nxt;
+        if (NT < 4) cur = nxt;
       }
     }
     // slices in order, one token at a time: red[rs][sg_local][j]
@@ -1787,8 +1791,9 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
   if (st != BITSMOE_OK) return st;
   if (d_in > (1 << 20)) return fail(BITSMOE_ERR_SHAPE, "moe_decode_in: d_in above 2^20");
   RoutingTables rt;
-  // Tokens per job: four share a decoded row, at 186 registers (two waves per
-  // SIMD); two (118 registers) while the experts with entries have at most two on
+  // Tokens per job: four share a decoded row, at 164 registers and without the
+  // fetch ahead (with it 182, two waves per SIMD: 76 against 65 us at 48 tokens of
+  // eight experts of 384 x 2048); two (116 registers) while the experts with entries have at most two on
   // average, when most of the four would go unused.
   int64_t busy = 0;
   if (offsets_host)
