@@ -358,6 +358,13 @@ int64_t plan_splits(int64_t kt, int64_t wg1) {
   return splits;
 }
 
+// Whether the GEMM stores the result itself (SymStore) where K is not split.
+// Its epilogue is 22 KB more code than PartialStore's, which a launch of a few
+// tiles spends its time fetching: 8 Grams of 256 take 89 us that way and 84
+// with partial tiles and their reduction, whose bytes (half a megabyte a
+// tile) cost more from about a hundred tiles on.
+constexpr int64_t kDirectTiles = 128;
+
 // Launches the symmetric split-K GEMM of p (tiles/splits already set) and
 // reduces it into out.
 // `batches` independent problems (blockIdx.z, operand strides bstride) write
@@ -379,7 +386,7 @@ bitsmoe_status run_symmetric(gemm::Problem p, int64_t d, double scale, OutT* out
     return fail(BITSMOE_ERR_SHAPE, std::string(name) + ": too many workgroups");
   p.flat = static_cast<int>(ntiles);
   dim3 grid(static_cast<unsigned>(ntiles * splits * batches), 1, 1);
-  if (splits == 1) {
+  if (splits == 1 && ntiles * batches >= kDirectTiles) {
     SymStore<OutT> epi{out, d, scale};
     KernelTimer timer(name, stream);
     hipLaunchKernelGGL((gemm::gemm_nt_kernel<GT, GT, 32, 4, SymStore<OutT>>), grid,
@@ -591,12 +598,13 @@ extern "C" bitsmoe_status bitsmoe_gram_routed(const void* X_dev, bitsmoe_dtype x
   const int passes = f32 ? 3 : 2;
   const int T = static_cast<int>(d_pad / GT);
   const int64_t ntiles = static_cast<int64_t>(T) * (T + 1) / 2;
-  // Where K is not split each expert's K ends with its own tokens, in the
+  // Where the GEMM stores the Grams each expert's K ends with its own tokens, in the
   // operands and in the GEMM, instead of the longest expert's: 781 -> 748 us at
   // 128 experts of 2048 with 256 tokens on average and 300 at most.  (The
   // launch moves about 3 GB at 4 TB/s; tiles of 256 x 128 with two workgroups
   // per compute unit read more and took 863.)
-  const bool direct = plan_splits(passes * npad / BK, ntiles * E) == 1 && ntiles * E <= INT32_MAX;
+  const bool direct = ntiles * E >= kDirectTiles && ntiles * E <= INT32_MAX &&
+                      plan_splits(passes * npad / BK, ntiles * E) == 1;
   dim3 tg(static_cast<unsigned>(npad / 64), static_cast<unsigned>((d + 63) / 64),
           static_cast<unsigned>(E));
   if (f32)

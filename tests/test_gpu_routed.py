@@ -65,11 +65,11 @@ def test_gram_routed(config):
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
-@pytest.mark.parametrize("d", [64, 256, 320, 576])
+@pytest.mark.parametrize("d", [64, 256, 320, 576, 4160])
 def test_grams_without_split(d, dt):
-    """K loops too short to split: the tiles are written by the GEMM itself
-    (part of a tile, a whole one, two and three tiles a side), for every
-    Gram of the library.  Bound: the products are exact but for the dropped
+    """K loops too short to split, for every Gram of the library: part of a
+    tile, a whole one, two and three tiles a side, and enough tiles (17 a
+    side) that the GEMM writes them itself.  Bound: the products are exact but for the dropped
     lo x lo term (2^-18) and the rounding of w x to two bf16 terms (2^-17),
     and at most 64 terms are added in fp32 (64 x 2^-24)."""
     say("grams without split", d, dt)
