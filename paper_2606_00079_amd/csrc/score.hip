@@ -134,56 +134,65 @@ __host__ __device__ __forceinline__ int64_t hoff_blocks(int64_t rt, int64_t nkt)
   constexpr int64_t per = SBM / gemm::kTileK;
   return rt * nkt - per * rt * (rt - 1) / 2;
 }
-// Returns the largest |H_ik| this thread read.
-__device__ __forceinline__ float hoff_block(const float* __restrict__ H, int64_t d, int64_t bx, int F,
-                                            uint16_t* __restrict__ Hoff, float* __restrict__ hdiag) {
-  const int64_t nkt = d / gemm::kTileK;
-  constexpr int64_t TB = static_cast<int64_t>(SBM) * gemm::kTileK;  // elements per tiled block
-  constexpr int kRuns = static_cast<int>(TB / 8 / 256);             // 8-entry runs per thread
-  int64_t rt = 0;
-  while (hoff_blocks(rt + 1, nkt) <= bx) ++rt;
-  const int64_t kt = rt * (SBM / gemm::kTileK) + (bx - hoff_blocks(rt, nkt));
+// One thread's part of such a block: its loads are issued before F is known.
+struct HoffBlock {
+  static constexpr int64_t TB = static_cast<int64_t>(SBM) * gemm::kTileK;  // elements per tiled block
+  static constexpr int kRuns = static_cast<int>(TB / 8 / 256);             // 8-entry runs per thread
+  int64_t rt, kt;
   float h[kRuns][8];
-#pragma unroll
-  for (int x = 0; x < kRuns; ++x) {
-    const int w = 8 * (static_cast<int>(threadIdx.x) + 256 * x);
-    const int64_t i = rt * SBM + w / gemm::kTileK;
-    const int64_t k = kt * gemm::kTileK + w % gemm::kTileK;
-#pragma unroll
-    for (int q = 0; q < 8; q += 4) {
-      float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      if (i < d) v = *reinterpret_cast<const float4*>(H + i * d + k + q);
-      h[x][q] = v.x; h[x][q + 1] = v.y; h[x][q + 2] = v.z; h[x][q + 3] = v.w;
-    }
+  // row and first column of run x
+  __device__ __forceinline__ int64_t row(int x) const {
+    return rt * SBM + 8 * (static_cast<int>(threadIdx.x) + 256 * x) / gemm::kTileK;
   }
-  uint16_t* dst = Hoff + (rt * nkt + kt) * TB;
-  float m = 0.0f;
+  __device__ __forceinline__ int64_t col(int x) const {
+    return kt * gemm::kTileK + 8 * (static_cast<int>(threadIdx.x) + 256 * x) % gemm::kTileK;
+  }
+  __device__ __forceinline__ void load(const float* __restrict__ H, int64_t d, int64_t bx) {
+    const int64_t nkt = d / gemm::kTileK;
+    rt = 0;
+    while (hoff_blocks(rt + 1, nkt) <= bx) ++rt;
+    kt = rt * (SBM / gemm::kTileK) + (bx - hoff_blocks(rt, nkt));
 #pragma unroll
-  for (int x = 0; x < kRuns; ++x) {
-    const int w = 8 * (static_cast<int>(threadIdx.x) + 256 * x);
-    const int64_t i = rt * SBM + w / gemm::kTileK;
-    const int64_t k = kt * gemm::kTileK + w % gemm::kTileK;
-    const int64_t it = i / gemm::kTileK;  // K tile of the row's own diagonal entry
-    const int e = kt > it ? F + 1 : F;
-    uint16_t v[8];
+    for (int x = 0; x < kRuns; ++x) {
+      const int64_t i = row(x), k = col(x);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      m = fmaxf(m, fabsf(h[x][q]));
-      v[q] = kt < it ? 0 : f32_to_f16_bits(ldexpf(h[x][q], e));
-      if (i == k + q) {
-        if (i < d) hdiag[i] = h[x][q];
-        v[q] = 0;
+      for (int q = 0; q < 8; q += 4) {
+        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (i < d) v = *reinterpret_cast<const float4*>(H + i * d + k + q);
+        h[x][q] = v.x; h[x][q + 1] = v.y; h[x][q + 2] = v.z; h[x][q + 3] = v.w;
       }
     }
-    uint4 pk;
-    pk.x = static_cast<uint32_t>(v[0]) | (static_cast<uint32_t>(v[1]) << 16);
-    pk.y = static_cast<uint32_t>(v[2]) | (static_cast<uint32_t>(v[3]) << 16);
-    pk.z = static_cast<uint32_t>(v[4]) | (static_cast<uint32_t>(v[5]) << 16);
-    pk.w = static_cast<uint32_t>(v[6]) | (static_cast<uint32_t>(v[7]) << 16);
-    *reinterpret_cast<uint4*>(dst + w) = pk;
   }
-  return m;
-}
+  // Returns the largest |H_ik| this thread read.
+  __device__ __forceinline__ float store(int64_t d, int F, uint16_t* __restrict__ Hoff,
+                                         float* __restrict__ hdiag) const {
+    uint16_t* dst = Hoff + (rt * (d / gemm::kTileK) + kt) * TB;
+    float m = 0.0f;
+#pragma unroll
+    for (int x = 0; x < kRuns; ++x) {
+      const int64_t i = row(x), k = col(x);
+      const int64_t it = i / gemm::kTileK;  // K tile of the row's own diagonal entry
+      const int e = kt > it ? F + 1 : F;
+      uint16_t v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        m = fmaxf(m, fabsf(h[x][q]));
+        v[q] = kt < it ? 0 : f32_to_f16_bits(ldexpf(h[x][q], e));
+        if (i == k + q) {
+          if (i < d) hdiag[i] = h[x][q];
+          v[q] = 0;
+        }
+      }
+      uint4 pk;
+      pk.x = static_cast<uint32_t>(v[0]) | (static_cast<uint32_t>(v[1]) << 16);
+      pk.y = static_cast<uint32_t>(v[2]) | (static_cast<uint32_t>(v[3]) << 16);
+      pk.z = static_cast<uint32_t>(v[4]) | (static_cast<uint32_t>(v[5]) << 16);
+      pk.w = static_cast<uint32_t>(v[6]) | (static_cast<uint32_t>(v[7]) << 16);
+      *reinterpret_cast<uint4*>(dst + 8 * (static_cast<int>(threadIdx.x) + 256 * x)) = pk;
+    }
+    return m;
+  }
+};
 // CHECK: F from the diagonal, checked; else from the maxima of habsmax_kernel.
 template <bool CHECK>
 __global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, int64_t d,
@@ -192,7 +201,9 @@ __global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, 
                                                    uint16_t* __restrict__ Hoff,
                                                    float* __restrict__ hdiag, int* __restrict__ hexp) {
   const int64_t z = blockIdx.y;  // one H per blockIdx.y
-  float top;                     // the maximum that F comes from
+  HoffBlock blk;
+  blk.load(H + z * d * d, d, blockIdx.x);
+  float top;  // the maximum that F comes from
   if constexpr (CHECK) {
     top = hmax[z].diag;
   } else {
@@ -204,7 +215,7 @@ __global__ __launch_bounds__(256) void hoff_kernel(const float* __restrict__ H, 
   const int e = exponent_above(top);
   const int F = kF16Top - 1 - e;
   if (blockIdx.x == 0 && threadIdx.x == 0) hexp[z] = F;
-  const float m = hoff_block(H + z * d * d, d, blockIdx.x, F, Hoff + z * d_pad * d, hdiag + z * d);
+  const float m = blk.store(d, F, Hoff + z * d_pad * d, hdiag + z * d);
   if constexpr (CHECK) {
     // (a zero diagonal bounds nothing: any entry has to be looked at)
     const float bound = top > 0.0f ? ldexpf(1.0f, e) : 0.0f;
@@ -219,8 +230,11 @@ __global__ __launch_bounds__(256) void hoff_redo_kernel(const float* __restrict_
   if (hmax[z].above == 0u) return;  // whole workgroup
   const int F = kF16Top - 1 - exponent_above(fmaxf(hmax[z].diag, __uint_as_float(hmax[z].above)));
   if (blockIdx.x == 0 && threadIdx.x == 0) hexp[z] = F;
-  for (int64_t bx = blockIdx.x; bx < blocks; bx += gridDim.x)
-    (void)hoff_block(H + z * d * d, d, bx, F, Hoff + z * d_pad * d, hdiag + z * d);
+  for (int64_t bx = blockIdx.x; bx < blocks; bx += gridDim.x) {
+    HoffBlock blk;
+    blk.load(H + z * d * d, d, bx);
+    (void)blk.store(d, F, Hoff + z * d_pad * d, hdiag + z * d);
+  }
 }
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
