@@ -665,14 +665,15 @@ def main(argv=None) -> int:
 
     def score_executed(p):
         # the kernel reads only the upper triangle of the symmetric H: row tile
-        # t (256 rows) multiplies the columns right of its diagonal block and,
-        # in that block, the 32 x 32 blocks at and right of the diagonal
+        # t (256 rows) multiplies the columns right of its diagonal block and
+        # that block, of whose first three 32-wide K tiles only the 32-row
+        # blocks at and above the diagonal
         d = p.spec.d_in
         rows = math.ceil(p.E * p.r * len(p.bits) / 256) * 256
 
         def entries(t):
             w = min(256, d - 256 * t)
-            return 256 * (d - 256 * t - w) + 1024 * (w // 32) * (w // 32 + 1) // 2
+            return 256 * (d - 256 * t - w) + 1024 * sum(q + 1 if q < 3 else 8 for q in range(w // 32))
         return sum(2.0 * rows * entries(t) for t in range(math.ceil(d / 256)))
     score_exec_flops = sum(score_executed(p) for p in layer)
     dgen_bytes = sum(p.E * p.r * p.spec.d_in * (4 + 2 * len(p.bits)) for p in layer)

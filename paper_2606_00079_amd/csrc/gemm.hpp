@@ -891,9 +891,10 @@ void gemm_nt_kernel(Problem p, Epi epi) {
   // K tile i (fragments of its first step already requested into set 0).
   // has_next: tile i + 1 exists; refill: tile i + STAGES - 1 exists (into
   // the buffer of tile i - 1, free since the barrier before this tile).
-  // tri (PAIRED, KB = 32): K tile i is one of the diagonal block, tile q = nk -
-  // 1 - i of it, which concerns the tile's rows up to 32 q + 31 only (A is
-  // zero below its 32-wide diagonal): of the BM / 32 row blocks, q + 1.
+  // tri (PAIRED, KB = 32): K tile i is one of the diagonal block's, which come
+  // last and in descending order: tile q = nk - 1 - i of it concerns the tile's
+  // rows up to 32 q + 31 only (A is zero below its 32-wide diagonal), q + 1 of
+  // the BM / 32 row blocks.
   auto tile = [&](int64_t i, auto has_next, auto refill, auto tail, auto tri) {
     constexpr int kWaveRows = 4 / NWN;  // waves that share the row blocks
     const int rows = (static_cast<int>(nk - i) - f.wm + kWaveRows - 1) / kWaveRows;
@@ -978,10 +979,12 @@ void gemm_nt_kernel(Problem p, Epi epi) {
       read_frags(Set0(), 0, 0);
       int64_t i = 0;
       if constexpr (PAIRED && KB == 32) {
-        // the last BM / KB tiles are the diagonal block's
+        // Only the tiles without a refill leave rows out.  With the block's
+        // others (2 to 4 of a wave's 4 row blocks) as well, the tests between the
+        // loads cost what the ops saved: 58 instead of 56 us at 465 units of 1216,
+        // 1027 instead of 1022 at 49152 of 2048.
         static_assert(BM / KB >= STAGES - 1, "the tiles without a refill are in the diagonal block");
-        for (; i + BM / KB < nk; ++i) tile(i, True(), True(), False(), False());
-        for (; i + STAGES - 1 < nk; ++i) tile(i, True(), True(), False(), True());
+        for (; i + STAGES - 1 < nk; ++i) tile(i, True(), True(), False(), False());
         for (; i + 1 < nk; ++i) tile(i, True(), False(), True(), True());
         tile(i, False(), False(), True(), True());
       } else {

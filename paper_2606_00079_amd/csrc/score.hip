@@ -84,8 +84,8 @@ __global__ __launch_bounds__(1024) void hdiagmax_kernel(const float* __restrict_
 
 // Partial maxima of |H_ik| over the upper block triangle (H is symmetric: a
 // bound for the off-diagonal maximum), one per block.  Row i counts from
-// its diagonal block on, columns 256 (i / 256) .. d - 1, so a wave takes
-// rows w and d - 1 - w: about the same number of entries for every wave.
+// its diagonal block on, columns 256 (i / 256) .. d - 1; a wave takes a row at a
+// time.
 __global__ __launch_bounds__(256) void habsmax_kernel(const float* __restrict__ H, int64_t d,
                                                       float* __restrict__ partial) {
   __shared__ float red[4];
@@ -111,10 +111,7 @@ __global__ __launch_bounds__(256) void habsmax_kernel(const float* __restrict__ 
     }
   };
   const int64_t stride = static_cast<int64_t>(gridDim.x) * 4;
-  for (int64_t w = static_cast<int64_t>(blockIdx.x) * 4 + wave; w < (d + 1) / 2; w += stride) {
-    row_max(w);
-    row_max(d - 1 - w);
-  }
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 4 + wave; i < d; i += stride) row_max(i);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
   if (lane == 0) red[wave] = m;
@@ -128,7 +125,8 @@ __global__ __launch_bounds__(256) void habsmax_kernel(const float* __restrict__ 
 // row block t uses column blocks t (weight 1) and t + 1, ... (weight 2, which
 // stands for the mirrored lower blocks).  Blocks left of a row tile's 256-wide
 // diagonal block are neither read nor written, those left of the 32-wide
-// diagonal inside it are zero (the GEMM leaves them out).  `bx` counts the 256 x 32 blocks of the layout.
+// diagonal inside it are zero (the GEMM leaves out those of the block's first
+// three K tiles, its last).  `bx` counts the 256 x 32 blocks of the layout.
 // Number of blocks at and right of the diagonal of row tiles 0 .. rt - 1.
 __host__ __device__ __forceinline__ int64_t hoff_blocks(int64_t rt, int64_t nkt) {
   constexpr int64_t per = SBM / gemm::kTileK;
@@ -819,7 +817,7 @@ bitsmoe_status loss_table_setup(int64_t d, int64_t R, int64_t units, bool row_st
 }
 
 // H -> scaled fp16 H_off and diag(H).  Bound by memory: 128 H of 2048 take
-// 490 us in all, against 274 + 425 with a pass for max |H| first.
+// about 435 us in all, against 274 + 425 with a pass for max |H| first.
 bitsmoe_status loss_table_hoff(const float* H_dev, const LossTable& t, hipStream_t s, const char* who) {
   const int64_t blocks = hoff_blocks(t.tiles_m, t.d / gemm::kTileK);
   if (blocks > INT32_MAX) return fail(BITSMOE_ERR_SHAPE, std::string(who) + ": too many blocks");
