@@ -27,11 +27,11 @@
 // three 64-bit words of 43 payload bits and the step's number in the upper
 // 21, each written and read by a relaxed device-scope atomic, so a reader
 // polls the data itself and needs no ordering between words.  Two slots
-// alternate: a workgroup publishes step i + 2 only after all its waves have
-// read step i + 1 of every workgroup, each of which published that after
-// all its waves had read step i.  All workgroups must be resident together:
-// the launch is cooperative, and a reader gives up after kSpinLimit polls
-// (reported as an error), so every workgroup ends.
+// alternate, and a workgroup whose rows are done publishes its last words and
+// leaves without reading anybody's: tridiag_steps.hpp has the rules and why two
+// slots are enough.  All workgroups must be resident together: the launch is
+// cooperative, and a reader gives up after kSpinLimit polls (reported as an
+// error), so every workgroup ends.
 #include <algorithm>
 #include <cmath>
 
@@ -39,12 +39,13 @@
 #include "common.hpp"
 #include "eig_wave.hpp"
 #include "internal.hpp"
+#include "tridiag_steps.hpp"
 
 namespace bitsmoe {
 namespace {
 
-constexpr int kRows = 8;          // rows per workgroup
-constexpr int kMaxSize = 2048;    // largest n (thread t owns columns t, t + threads, ...)
+constexpr int kRows = kTridiagRows;
+constexpr int kMaxSize = 2048;  // largest n (thread t owns columns t, t + threads, ...)
 constexpr int kSpinLimit = 1 << 22;
 
 constexpr uint64_t kMask43 = (uint64_t{1} << 43) - 1;
@@ -123,7 +124,6 @@ __global__ __launch_bounds__(kThreads) void tridiag_kernel(
   __syncthreads();
 
   for (int i = 0; i + 1 < n; ++i) {
-    if (r0 + kRows <= i + 1) return;     // no row right of column i left (never the last workgroup)
     const int kmin = (i + 1) / kThreads;  // columns below kmin kThreads are done
     const int to = (i + 1) % kThreads;    // thread (and k = kmin) of column i + 1
     double* sa = s_a[i & 1];
@@ -158,13 +158,13 @@ __global__ __launch_bounds__(kThreads) void tridiag_kernel(
     lds_barrier();
     const uint64_t epoch = static_cast<uint64_t>(i + 1) << 43;
     uint64_t* slot = ex + (i & 1) * 3 * n;
-    if (wave == 0 && i + 2 < n) {
+    if (wave == 0 && tridiag_exchanges(n, i)) {
       const double q = sumw(part[lane & 7]);
       const uint64_t P = __builtin_bit_cast(uint64_t, q);
       const uint64_t Q = __builtin_bit_cast(uint64_t, sa[lane & 7]);
       if (lane < kRows) {
         s_q[lane] = q;
-        if (rl > i && rl < n) {
+        if (tridiag_word_live(n, i, rl)) {
           store_word(slot + rl, epoch | (P & kMask43));
           store_word(slot + n + rl, epoch | (P >> 43) | ((Q & ((uint64_t{1} << 22) - 1)) << 21));
           store_word(slot + 2 * n + rl, epoch | (Q >> 22));
@@ -180,6 +180,13 @@ __global__ __launch_bounds__(kThreads) void tridiag_kernel(
       sc = 1.0 / (alpha - beta);
     }
     vl = rl > i + 1 ? xl * sc : (rl == i + 1 ? 1.0 : 0.0);
+    auto store_v = [&] {
+      if (wave == 0 && lane < kRows && rl > i && rl < n) V[static_cast<int64_t>(i) * n + rl] = vl;
+    };
+    if (tridiag_leaves(n, i, r0)) {  // whole workgroup
+      store_v();
+      return;
+    }
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
       const int c = tid + kThreads * k;
@@ -187,7 +194,7 @@ __global__ __launch_bounds__(kThreads) void tridiag_kernel(
     }
     // everybody's products and column entries at this thread's columns
     uint64_t g[CPT][3];
-    if (i + 2 < n) {
+    if (tridiag_exchanges(n, i)) {
       // (a poll that comes too early costs a whole further one)
       __builtin_amdgcn_s_sleep(8);
       for (int spin = 0;; ++spin) {
@@ -195,14 +202,14 @@ __global__ __launch_bounds__(kThreads) void tridiag_kernel(
 #pragma unroll
         for (int k = 0; k < CPT; ++k) {
           const int c = tid + kThreads * k;
-          if (k < kmin || c <= i || c >= n) continue;
+          if (k < kmin || !tridiag_word_live(n, i, c)) continue;
 #pragma unroll
           for (int h = 0; h < 3; ++h) g[k][h] = load_word(slot + h * n + c);
         }
 #pragma unroll
         for (int k = 0; k < CPT; ++k) {
           const int c = tid + kThreads * k;
-          if (k < kmin || c <= i || c >= n) continue;
+          if (k < kmin || !tridiag_word_live(n, i, c)) continue;
 #pragma unroll
           for (int h = 0; h < 3; ++h) all &= (g[k][h] ^ epoch) <= kMask43;
         }
@@ -215,13 +222,13 @@ __global__ __launch_bounds__(kThreads) void tridiag_kernel(
       }
     }
     // (these stores come after the polls, which would wait for them)
-    if (wave == 0 && lane < kRows && rl > i && rl < n) V[static_cast<int64_t>(i) * n + rl] = vl;
+    store_v();
     if (last && tid == 0) {
       dvec[i] = dcur;
       evec[i] = beta;
       tau[i] = t;
     }
-    if (i + 2 == n) {
+    if (!tridiag_exchanges(n, i)) {
       // x has a single entry: tau = 0, nothing is left to update
       if (last && tid == 0) dvec[n - 1] = sa[n - 1 - r0];
       return;
@@ -231,7 +238,7 @@ __global__ __launch_bounds__(kThreads) void tridiag_kernel(
     for (int k = 0; k < CPT; ++k) {
       const int c = tid + kThreads * k;
       p[k] = a[k] = 0.0;
-      if (k < kmin || c <= i || c >= n) continue;
+      if (k < kmin || !tridiag_word_live(n, i, c)) continue;
       a[k] = second_f64(g[k][1], g[k][2]);
       const double q = first_f64(g[k][0], g[k][1]);
       p[k] = fma(q, sc, a[k]);
