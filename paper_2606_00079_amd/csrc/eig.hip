@@ -567,14 +567,47 @@ __global__ __launch_bounds__(256) void finish_kernel(const double* __restrict__ 
   for (int64_t j = threadIdx.x; j < n; j += 256) Ut[k * n + j] = static_cast<float>(sg * z[j]);
 }
 
+// The panel form of the reduction: M [n][n] -> d, e, tau and the reflectors by
+// rows in A [n][n] (Wp [NB][n], ybv [n + 2 NB], vbuf [n] are work space).
+bitsmoe_status tridiag_panels(const double* M, int64_t n, double* A, double* Wp, double* ybv,
+                              double* dvec, double* evec, double* tau, double* vbuf, hipStream_t s) {
+  const hipError_t he = hipMemcpyAsync(A, M, static_cast<size_t>(n * n) * 8, hipMemcpyDeviceToDevice, s);
+  if (he != hipSuccess) return device_error("shared_basis_gpu: copy of M", he);
+  KernelTimer timer("eig_tridiag", s);
+  for (int64_t j0 = 0; j0 < n - 1; j0 += NB) {
+    const int64_t pe = std::min<int64_t>(j0 + NB, n - 1);
+    const bool full = j0 + NB <= n - 1;  // a trailing update follows the panel
+    for (int64_t i = j0; i < pe; ++i) {
+      const int c = static_cast<int>(i - j0);
+      const int64_t m = n - i - 1;
+      const int64_t R = m + 2 * c;
+      hipLaunchKernelGGL(trsymv_kernel, dim3(static_cast<unsigned>((R + 7) / 8)), dim3(256), 0, s,
+                         A, Wp, n, i, j0, c, ybv, dvec, evec, tau, vbuf);
+      const int do_row = (full && c == NB - 1) ? 0 : 1;
+      hipLaunchKernelGGL(trw_kernel, dim3(static_cast<unsigned>((m + 63) / 64)), dim3(256), 0, s,
+                         A, Wp, n, i, j0, c, ybv, tau, vbuf, do_row);
+    }
+    if (full) {
+      const int64_t sidx = j0 + NB;
+      const unsigned tiles = static_cast<unsigned>((n - sidx + 63) / 64);
+      hipLaunchKernelGGL(trail_kernel, dim3(tiles, tiles), dim3(256), 0, s, A, A + j0 * n, Wp, n,
+                         sidx);
+    }
+  }
+  hipLaunchKernelGGL(last_diag_kernel, dim3(1), dim3(64), 0, s, A, n, dvec);
+  BITSMOE_LAUNCH_CHECK("shared_basis_gpu: tridiagonal reduction");
+  return BITSMOE_OK;
+}
+
 }  // namespace
 }  // namespace bitsmoe
 
 using namespace bitsmoe;
 
-extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t d_out, int64_t r,
-                                                   float* Ut_dev, double* eigvals_host,
-                                                   double* host_ms, void* stream) {
+extern "C" bitsmoe_status bitsmoe_shared_basis_gpu_polls(const double* M_dev, int64_t d_out, int64_t r,
+                                                         float* Ut_dev, double* eigvals_host,
+                                                         double* host_ms, int poll_limit,
+                                                         int* gave_up_host, void* stream) {
   auto t0 = std::chrono::steady_clock::now();
   if (!M_dev || !Ut_dev) return fail(BITSMOE_ERR_ARG, "shared_basis_gpu: null pointer");
   if (!aligned16({M_dev, Ut_dev}))
@@ -622,77 +655,60 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t 
   } catch (...) {
     return fail(BITSMOE_ERR_NOMEM, "shared_basis_gpu: host allocation failed");
   }
-  hipError_t he;
-  // 1. tridiagonal reduction: in one launch where the matrix fits the
-  // register files (n <= 2048 on 256 compute units; 28.9 -> 6.4 ms at n =
-  // 2048; up to 128 those of one compute unit), else a panel at a time
-  const bool one_cu = tridiag_small_fits(n);
-  bool resident = !one_cu && tridiag_resident_fits(n);
-  if (one_cu) {
-    KernelTimer timer("eig_tridiag", stream);
-    tridiag_small(M_dev, n, A, dvec, evec, tau, stream);
-  } else if (resident) {
-    KernelTimer timer("eig_tridiag", stream);
-    resident = tridiag_resident(M_dev, n, A, dvec, evec, tau, exch, err, stream);
-  }
-  if (!one_cu && !resident) {
-    he = hipMemcpyAsync(A, M_dev, static_cast<size_t>(n * n) * 8, hipMemcpyDeviceToDevice, s);
-    if (he != hipSuccess) return device_error("shared_basis_gpu: copy of M", he);
-    KernelTimer timer("eig_tridiag", stream);
-    for (int64_t j0 = 0; j0 < n - 1; j0 += NB) {
-      const int64_t pe = std::min<int64_t>(j0 + NB, n - 1);
-      const bool full = j0 + NB <= n - 1;  // a trailing update follows the panel
-      for (int64_t i = j0; i < pe; ++i) {
-        const int c = static_cast<int>(i - j0);
-        const int64_t m = n - i - 1;
-        const int64_t R = m + 2 * c;
-        hipLaunchKernelGGL(trsymv_kernel, dim3(static_cast<unsigned>((R + 7) / 8)), dim3(256), 0, s,
-                           A, Wp, n, i, j0, c, ybv, dvec, evec, tau, vbuf);
-        const int do_row = (full && c == NB - 1) ? 0 : 1;
-        hipLaunchKernelGGL(trw_kernel, dim3(static_cast<unsigned>((m + 63) / 64)), dim3(256), 0, s,
-                           A, Wp, n, i, j0, c, ybv, tau, vbuf, do_row);
-      }
-      if (full) {
-        const int64_t sidx = j0 + NB;
-        const unsigned tiles = static_cast<unsigned>((n - sidx + 63) / 64);
-        hipLaunchKernelGGL(trail_kernel, dim3(tiles, tiles), dim3(256), 0, s, A, A + j0 * n, Wp, n,
-                           sidx);
-      }
-    }
-    hipLaunchKernelGGL(last_diag_kernel, dim3(1), dim3(64), 0, s, A, n, dvec);
-  }
-  BITSMOE_LAUNCH_CHECK("shared_basis_gpu: tridiagonal reduction");
-  // 2. eigenpairs of T
-  {
-    KernelTimer timer("eig_tri_solve", stream);
-    st = tri_eigenpairs(dvec, evec, n, r, wd, Zt, info, bad, tri, stream);
-    if (st != BITSMOE_OK) return st;
-  }
-  // The panels' compact forms, while the host reads the eigenvalues.  Up to
-  // n = 2048 a workgroup holds whole vectors in registers (6.2 -> 0.96 ms).
-  const bool small_back = backtransform_fits(n);
-  if (small_back) {
-    KernelTimer timer("eig_backtransform", stream);
-    st = backtransform_panels(A, tau, n, T, stream);
-    if (st != BITSMOE_OK) return st;
-  } else {
-    KernelTimer timer("eig_backtransform", stream);
-    hipLaunchKernelGGL(panel_gram_kernel, dim3(NB / 8, static_cast<unsigned>(npan)), dim3(256), 0, s,
-                       A, n, G);
-    hipLaunchKernelGGL(tfactor_kernel, dim3(static_cast<unsigned>(npan)), dim3(64), 0, s, G, tau, n, T);
-    BITSMOE_LAUNCH_CHECK("shared_basis_gpu: compact forms");
-  }
-  he = hipMemcpyAsync(res.data(), wd, res_words * 8, hipMemcpyDeviceToHost, s);
-  if (he == hipSuccess) he = hipStreamSynchronize(s);
-  if (he != hipSuccess) return device_error("shared_basis_gpu: copy of the eigenvalues", he);
+  hipError_t he = hipSuccess;
   const double* w = res.data();
   const double* info_h = w + r;
   const uint8_t* bad_h = reinterpret_cast<const uint8_t*>(info_h + 9);
-  if (resident) {
+  const bool small_back = backtransform_fits(n);
+  // Steps 1 and 2, at most twice: where the workgroups of the one-launch
+  // reduction did not all run together (a device busy with other work for
+  // seconds) a reader gives up, which the host learns with the eigenvalues,
+  // and the panel form takes over from M.
+  const bool one_cu = tridiag_small_fits(n);
+  bool resident = !one_cu && tridiag_resident_fits(n);
+  for (int gave_up = 0;; gave_up = 1) {
+    // 1. tridiagonal reduction: in one launch where the matrix fits the
+    // register files (n <= 2048 on 256 compute units; 28.9 -> 6.4 ms at n =
+    // 2048; up to 128 those of one compute unit), else a panel at a time
+    if (one_cu) {
+      KernelTimer timer("eig_tridiag", stream);
+      tridiag_small(M_dev, n, A, dvec, evec, tau, stream);
+    } else if (resident) {
+      KernelTimer timer("eig_tridiag", stream);
+      resident = tridiag_resident(M_dev, n, A, dvec, evec, tau, exch, err, poll_limit, stream);
+    }
+    if (!one_cu && !resident) {
+      st = tridiag_panels(M_dev, n, A, Wp, ybv, dvec, evec, tau, vbuf, s);
+      if (st != BITSMOE_OK) return st;
+    }
+    BITSMOE_LAUNCH_CHECK("shared_basis_gpu: tridiagonal reduction");
+    // 2. eigenpairs of T
+    {
+      KernelTimer timer("eig_tri_solve", stream);
+      st = tri_eigenpairs(dvec, evec, n, r, wd, Zt, info, bad, tri, stream);
+      if (st != BITSMOE_OK) return st;
+    }
+    // The panels' compact forms, while the host reads the eigenvalues.  Up to
+    // n = 2048 a workgroup holds whole vectors in registers (6.2 -> 0.96 ms).
+    if (small_back) {
+      KernelTimer timer("eig_backtransform", stream);
+      st = backtransform_panels(A, tau, n, T, stream);
+      if (st != BITSMOE_OK) return st;
+    } else {
+      KernelTimer timer("eig_backtransform", stream);
+      hipLaunchKernelGGL(panel_gram_kernel, dim3(NB / 8, static_cast<unsigned>(npan)), dim3(256), 0, s,
+                         A, n, G);
+      hipLaunchKernelGGL(tfactor_kernel, dim3(static_cast<unsigned>(npan)), dim3(64), 0, s, G, tau, n, T);
+      BITSMOE_LAUNCH_CHECK("shared_basis_gpu: compact forms");
+    }
+    he = hipMemcpyAsync(res.data(), wd, res_words * 8, hipMemcpyDeviceToHost, s);
+    if (he == hipSuccess) he = hipStreamSynchronize(s);
+    if (he != hipSuccess) return device_error("shared_basis_gpu: copy of the eigenvalues", he);
     int e = 0;
-    std::memcpy(&e, info_h + 8, sizeof e);
-    if (e)
-      return fail(BITSMOE_ERR_DEVICE, "shared_basis_gpu: the tridiagonal reduction's workgroups lost contact");
+    if (resident) std::memcpy(&e, info_h + 8, sizeof e);
+    if (gave_up_host) *gave_up_host = gave_up;
+    if (e == 0) break;
+    resident = false;
   }
   if (info_h[6] != 0.0) return fail(BITSMOE_ERR_NUMERIC, "shared_basis_gpu: M is not finite");
   // Vectors of clustered eigenvalues (closer than 1e-7 of the norm: a twisted
@@ -773,4 +789,11 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t 
     *host_ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
   }
   return ok();
+}
+
+extern "C" bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t d_out, int64_t r,
+                                                   float* Ut_dev, double* eigvals_host,
+                                                   double* host_ms, void* stream) {
+  return bitsmoe_shared_basis_gpu_polls(M_dev, d_out, r, Ut_dev, eigvals_host, host_ms, kTridiagPolls,
+                                        nullptr, stream);
 }

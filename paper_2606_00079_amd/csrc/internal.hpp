@@ -55,11 +55,14 @@ class KernelTimer {
 // launch (tridiag.hip): the diagonals d [n] and e [n-1], tau [n-1] and the
 // reflectors by rows into V [n][n].  `fits`: whether this device holds an
 // n x n matrix that way; `work` has `bytes` bytes, *err is nonzero after a
-// run that failed.  False if the launch was refused (nothing was computed).
+// run in which a reader of the exchange gave up, after `poll_limit` polls (the
+// outputs are then of no use; M is as it was).  False if the launch was refused
+// (nothing was computed).
+constexpr int kTridiagPolls = 1 << 22;  // (seconds)
 bool tridiag_resident_fits(int64_t n);
 size_t tridiag_resident_bytes(int64_t n);
 bool tridiag_resident(const double* M, int64_t n, double* V, double* dvec, double* evec,
-                      double* tau, void* work, int* err, void* stream);
+                      double* tau, void* work, int* err, int poll_limit, void* stream);
 
 // The same by one workgroup, for n that `fits`.
 bool tridiag_small_fits(int64_t n);
@@ -86,6 +89,14 @@ bitsmoe_status backtransform_panels(const double* V, const double* tau, int64_t 
                                     void* stream);
 bitsmoe_status backtransform(const double* V, const double* T, const double* Zt, int64_t n, int64_t r,
                              float* Ut, void* stream);
+
+// bitsmoe_shared_basis_gpu with its own poll limit for the one-launch reduction;
+// *gave_up_host (may be null) is 1 where a reader gave up and the panel form took
+// over.  For the test of that route; not part of the interface.
+extern "C" bitsmoe_status bitsmoe_shared_basis_gpu_polls(const double* M_dev, int64_t d_out, int64_t r,
+                                                         float* Ut_dev, double* eigvals_host,
+                                                         double* host_ms, int poll_limit,
+                                                         int* gave_up_host, void* stream);
 
 // True when every pointer is 16-byte aligned (the kernels use 16-byte
 // vector accesses on device buffers).

@@ -30,8 +30,8 @@
 // alternate, and a workgroup whose rows are done publishes its last words and
 // leaves without reading anybody's: tridiag_steps.hpp has the rules and why two
 // slots are enough.  All workgroups must be resident together: the launch is
-// cooperative, and a reader gives up after kSpinLimit polls (reported as an
-// error), so every workgroup ends.
+// cooperative, and a reader gives up after poll_limit polls (*err; the caller
+// then takes the other reduction), so every workgroup ends.
 #include <algorithm>
 #include <cmath>
 
@@ -46,7 +46,6 @@ namespace {
 
 constexpr int kRows = kTridiagRows;
 constexpr int kMaxSize = 2048;  // largest n (thread t owns columns t, t + threads, ...)
-constexpr int kSpinLimit = 1 << 22;
 
 constexpr uint64_t kMask43 = (uint64_t{1} << 43) - 1;
 
@@ -81,7 +80,7 @@ template <int kThreads, int CPT>
 __global__ __launch_bounds__(kThreads) void tridiag_kernel(
     const double* __restrict__ M, int n, double* __restrict__ V, double* __restrict__ dvec,
     double* __restrict__ evec, double* __restrict__ tau, uint64_t* __restrict__ ex,
-    int* __restrict__ err) {
+    int* __restrict__ err, int poll_limit) {
   constexpr int W = kThreads / 64;
   // sums over the waves; this workgroup's products and column entries (the
   // latter by the step's parity: they are read while the next step's are
@@ -214,7 +213,7 @@ __global__ __launch_bounds__(kThreads) void tridiag_kernel(
           for (int h = 0; h < 3; ++h) all &= (g[k][h] ^ epoch) <= kMask43;
         }
         if (all) break;
-        if (spin >= kSpinLimit) {
+        if (spin >= poll_limit) {
           s_abort = 1;
           *err = 1;
           break;
@@ -447,7 +446,7 @@ size_t tridiag_resident_bytes(int64_t n) {
 }
 
 bool tridiag_resident(const double* M, int64_t n64, double* V, double* dvec, double* evec,
-                      double* tau, void* work, int* err, void* stream) {
+                      double* tau, void* work, int* err, int poll_limit, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   int n = static_cast<int>(n64);
   uint64_t* ex = static_cast<uint64_t*>(work);
@@ -467,7 +466,7 @@ bool tridiag_resident(const double* M, int64_t n64, double* V, double* dvec, dou
   hipLaunchKernelGGL(tridiag_clear_kernel, dim3(static_cast<unsigned>((words + 255) / 256)),
                      dim3(256), 0, s, ex, words, err);
   if (hipGetLastError() != hipSuccess) return false;
-  void* args[] = {&M, &n, &V, &dvec, &evec, &tau, &ex, &err};
+  void* args[] = {&M, &n, &V, &dvec, &evec, &tau, &ex, &err, &poll_limit};
   const hipError_t e = hipLaunchCooperativeKernel(
       fn, dim3(static_cast<unsigned>((n + kRows - 1) / kRows)), dim3(static_cast<unsigned>(threads)), args, 0, s);
   if (e != hipSuccess) {

@@ -7,6 +7,7 @@ oracle's; inside clusters, where eigenvectors are not unique, the residual
 ||M U - U Lambda|| / ||M|| and orthonormality within fp32 rounding and the
 subspace of the separated leading eigenvalues within 1e-6 (projector norm).
 """
+import ctypes
 import sys
 
 import numpy as np
@@ -86,6 +87,26 @@ def test_resident_reduction_edges(n, r):
     say("resident edges", n, r)
     M = _separated(n, seed=n)
     Ut, ev, _ = bm.shared_basis_gpu(torch.from_numpy(M).to(DEV), r)
+    Uref, lref = oracle.shared_basis(M, r)
+    assert np.max(np.abs(ev - lref)) <= 1e-11 * n
+    assert np.max(np.abs(Ut.cpu().numpy() - Uref)) <= 2e-6
+
+
+@pytest.mark.parametrize("n,r", [(129, 20), (300, 300), (2048, 9)])
+def test_reduction_whose_readers_give_up(n, r):
+    """A poll limit of 0 makes readers of the one-launch reduction's exchange
+    give up at once: the call returns the panel form's result, not an error."""
+    say("give up", n, r)
+    M = _separated(n, seed=n)
+    Md = torch.from_numpy(M).to(DEV)
+    Ut = torch.full((r, n), float("nan"), dtype=torch.float32, device=DEV)
+    ev, gave_up = np.empty(r), ctypes.c_int(-1)
+    st = bm.lib().bitsmoe_shared_basis_gpu_polls(
+        ctypes.c_void_p(Md.data_ptr()), ctypes.c_int64(n), ctypes.c_int64(r),
+        ctypes.c_void_p(Ut.data_ptr()), ev.ctypes.data_as(ctypes.c_void_p), None, ctypes.c_int(0),
+        ctypes.byref(gave_up), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == 0, bm.last_error()
+    assert gave_up.value == 1
     Uref, lref = oracle.shared_basis(M, r)
     assert np.max(np.abs(ev - lref)) <= 1e-11 * n
     assert np.max(np.abs(Ut.cpu().numpy() - Uref)) <= 2e-6
