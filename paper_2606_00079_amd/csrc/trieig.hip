@@ -12,7 +12,8 @@
 // by a power of two, p is rescaled by one every eight rows, and couplings
 // below 1e-25 are raised to it: eight rows then move p by less than the
 // exponent's range, and a zero p_j is followed by p_{j+1} = -e^2 p_{j-1} of
-// the sign that counts it once.
+// the sign that counts it once.  (Beside a norm of 1/2 or more 1e-25 is far
+// below an ulp; T = 0 has no norm to compare it with and is answered as such.)
 //
 // Before: counts by quotients (a division per row on the dependent chain:
 // 2.39 ms at n = 2048, r = 1024; 0.70 ms at 768, r = 384) and three inverse
@@ -154,6 +155,10 @@ __global__ __launch_bounds__(64) void tri_bisect_kernel(const double* __restrict
                                                         double* __restrict__ w) {
   const int lane = threadIdx.x;
   const int64_t t = t0 + blockIdx.x;
+  if (info[2] == 0.0) {  // T = 0
+    if (lane == 0) ws[blockIdx.x] = w[blockIdx.x] = 0.0;
+    return;
+  }
   double lo = info[0], hi = info[1];
   const double atol = 2.0 * 2.220446049250313e-16 * info[2];
   for (int it = 0; it < 64 && hi - lo > atol; ++it) {
@@ -208,13 +213,20 @@ template <bool IN_LDS>
 __global__ __launch_bounds__(128) void tri_vec_kernel(const double* __restrict__ de,
                                                       const double* __restrict__ rev,
                                                       const double* __restrict__ es, int64_t n,
-                                                      int64_t np, const double* __restrict__ ws,
+                                                      int64_t np, const double* __restrict__ info,
+                                                      const double* __restrict__ ws,
                                                       double* __restrict__ work,
                                                       double* __restrict__ Zt,
                                                       uint8_t* __restrict__ bad) {
   extern __shared__ double lds[];
   __shared__ double s_v[2];
   __shared__ int64_t s_i[2];
+  if (info[2] == 0.0) {  // T = 0: unit vectors
+    double* z = Zt + blockIdx.x * n;
+    for (int64_t j = threadIdx.x; j < n; j += 128) z[j] = j == n - gridDim.x + blockIdx.x ? 1.0 : 0.0;
+    if (threadIdx.x == 0) bad[blockIdx.x] = 0;
+    return;
+  }
   const int64_t len = row_at(np) + 1;
   double* pf = IN_LDS ? lds : work + blockIdx.x * 2 * len;  // rows from the top
   double* pb = pf + len;                                    // rows from the bottom
@@ -353,11 +365,11 @@ bitsmoe_status tri_eigenpairs(const double* d, const double* e, int64_t n, int64
                      info, ws, w);
   if (np <= kVecLds)
     hipLaunchKernelGGL(tri_vec_kernel<true>, dim3(static_cast<unsigned>(r)), dim3(128),
-                       static_cast<size_t>(2 * (row_at(np) + 1)) * 8, s, de, rev, es, n, np, ws, work,
+                       static_cast<size_t>(2 * (row_at(np) + 1)) * 8, s, de, rev, es, n, np, info, ws, work,
                        Zt, bad);
   else
     hipLaunchKernelGGL(tri_vec_kernel<false>, dim3(static_cast<unsigned>(r)), dim3(128), 0, s, de, rev,
-                       es, n, np, ws, work, Zt, bad);
+                       es, n, np, info, ws, work, Zt, bad);
   BITSMOE_LAUNCH_CHECK("shared_basis_gpu: tridiagonal eigenpairs");
   return BITSMOE_OK;
 }

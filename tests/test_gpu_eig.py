@@ -144,6 +144,17 @@ def test_rank_deficient_and_repeated():
     _check_invariants(M2, Ut2.cpu().numpy(), ev2, 10)
 
 
+@pytest.mark.parametrize("n,r", [(1, 1), (2, 2), (64, 33), (130, 130), (300, 7), (2049, 3)])
+def test_zero_m(n, r):
+    """M = 0, in every form of the reduction: every eigenvalue is 0 and the
+    vectors are orthonormal (unit vectors, as LAPACK's are)."""
+    say("zero", n, r)
+    Ut, ev, _ = bm.shared_basis_gpu(torch.zeros((n, n), dtype=torch.float64, device=DEV), r)
+    assert np.all(ev == 0.0)
+    U = Ut.cpu().numpy().astype(np.float64)
+    assert np.array_equal(U @ U.T, np.eye(r))
+
+
 def _signal_projector_close(Ua, Ub, k):
     A = np.asarray(Ua, np.float64)[:k]
     B = np.asarray(Ub, np.float64)[:k]
