@@ -1794,11 +1794,13 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
   // Tokens per job: four share a decoded row, at 164 registers and without the
   // fetch ahead (with it 182, two waves per SIMD: 76 against 65 us at 48 tokens of
   // eight experts of 384 x 2048); two (116 registers) while the experts with entries have at most two on
-  // average, when most of the four would go unused.
+  // average, when most of the four would go unused.  (Jobs of two are more: not
+  // where they could pass the limit of 65535, which is meant for jobs of four.)
   int64_t busy = 0;
   if (offsets_host)
     for (int64_t e = 0; e < E; ++e) busy += offsets_host[e + 1] > offsets_host[e] ? 1 : 0;
-  const int tmax = offsets_host && offsets_host[E] <= 2 * busy ? 2 : 4;
+  const int64_t nnz = offsets_host ? offsets_host[E] : 0;
+  const int tmax = nnz <= 2 * busy && (nnz + busy) / 2 <= 65535 ? 2 : 4;
   st = build_routing("moe_decode_in", E, B, offsets_host, tokens_host, weights_host, tmax, &rt);
   if (st != BITSMOE_OK) return st;
   // segments of 16 outputs: SEGW per workgroup (up to 256), RSL = 256 / SEGW

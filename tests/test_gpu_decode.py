@@ -242,6 +242,28 @@ def test_moe_decode_in_edges(E, r, d_out, d_in, B, k, G, widths):
     assert relfro(Y, ref) <= REL
 
 
+def test_moe_decode_in_many_experts():
+    """65535 experts, every other one with three entries and the others with
+    one: two entries per expert on average, but 98302 jobs of up to two (the
+    limit is 65535 chunks of four, which they meet exactly)."""
+    say("decode_in many experts")
+    E, r, d, B, G = 65535, 1, 64, 64, 64
+    g = np.random.default_rng(12)
+    C = g.standard_normal((E * r, d)).astype(np.float32)
+    bits_u = g.choice((1, 2, 16), size=E * r).astype(np.uint8)
+    codes, params, off = oracle.pack(C, bits_u, G)
+    Vt = g.standard_normal((r, 4)).astype(np.float32)
+    X = g.standard_normal((B, 4)).astype(np.float32)
+    offs = np.r_[0, np.cumsum(np.where(np.arange(E) % 2 == 0, 1, 3))].astype(np.int64)
+    tok = (np.arange(offs[-1]) % B).astype(np.int32)
+    w = g.random(offs[-1]).astype(np.float32)
+    Y = bm.moe_decode_in(torch.from_numpy(codes.view(np.int64)).to(DEV), torch.from_numpy(params.view(np.int16)).to(DEV),
+                         torch.from_numpy(bits_u).to(DEV), torch.from_numpy(off).to(DEV), int(off[-1]), E, r, d, G,
+                         torch.from_numpy(Vt).to(DEV), torch.from_numpy(X).to(DEV), (offs, tok, w)).cpu().numpy()
+    Chat = decode.dequantized_factors(codes, params, bits_u, d, G)
+    assert relfro(Y, decode.moe_decode_in(Chat, r, Vt, X, offs, tok, w)) <= REL
+
+
 @pytest.mark.parametrize("B", [16, 32, 33, 64, 65, 100])
 @pytest.mark.parametrize("d_out", [80, 4160])
 def test_moe_decode_y_tiles(B, d_out):
