@@ -1343,13 +1343,13 @@ struct RoutingUpload {
     const size_t job_bytes = static_cast<size_t>(std::max<int64_t>(rt.njobs, 1)) * 32;
     const size_t pidx_bytes = static_cast<size_t>(B * rt.kmax) * 8;
     const size_t w_bytes = (static_cast<size_t>(rt.nnz) * 4 + 15) / 16 * 16;
+    host.assign(job_bytes + pidx_bytes + w_bytes, 0);
     bitsmoe_status st;
     tab = static_cast<char*>(scratch(kScratchMisc, job_bytes + pidx_bytes + w_bytes + 64, stream, &st));
     if (!tab) return st;
     jobs = reinterpret_cast<int4*>(tab);
     pidx = reinterpret_cast<int64_t*>(tab + job_bytes);
     w = reinterpret_cast<float*>(tab + job_bytes + pidx_bytes);
-    host.assign(job_bytes + pidx_bytes + w_bytes, 0);
     if (rt.njobs > 0) std::memcpy(host.data(), rt.jobs.data(), static_cast<size_t>(rt.njobs) * 32);
     std::memcpy(host.data() + job_bytes, rt.pidx.data(), pidx_bytes);
     if (rt.nnz > 0)
@@ -1643,7 +1643,7 @@ extern "C" bitsmoe_status bitsmoe_moe_decode(const uint64_t* codes_dev, const ui
                                              const float* Ut_dev, int64_t d_out, const float* X_dev,
                                              int64_t B, const int64_t* offsets_host,
                                              const int32_t* tokens_host, const float* weights_host,
-                                             float* Y_dev, void* stream) {
+                                             float* Y_dev, void* stream) try {
   bitsmoe_status st = check_decode("moe_decode", codes_dev, params_dev, bits_dev, word_offsets_dev,
                                    Ut_dev, X_dev, Y_dev, total_words, E, r, d_in, group, d_out, B);
   if (st != BITSMOE_OK) return st;
@@ -1698,6 +1698,8 @@ extern "C" bitsmoe_status bitsmoe_moe_decode(const uint64_t* codes_dev, const ui
                        total_words, E, r, d_in, group, Ut_dev, d_out, X_dev, B, up.jobs, nullptr, 1,
                        up.w, up.pidx, static_cast<int>(rt.kmax), zp, Y_dev,
                        static_cast<hipStream_t>(stream));
+} catch (...) {
+  return fail(BITSMOE_ERR_NOMEM, "moe_decode: host allocation failed");
 }
 
 extern "C" bitsmoe_status bitsmoe_moe_decode_topk(const uint64_t* codes_dev, const uint16_t* params_dev,
@@ -1782,7 +1784,7 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
                                                 const int64_t* offsets_host,
                                                 const int32_t* tokens_host,
                                                 const float* weights_host, float* Y_dev,
-                                                void* stream) {
+                                                void* stream) try {
   // the units have d_out entries here: the shape rules of the packed rows
   // apply to d_out, the basis rows and tokens have d_in
   bitsmoe_status st = check_decode("moe_decode_in", codes_dev, params_dev, bits_dev,
@@ -1866,4 +1868,6 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
   }
   BITSMOE_LAUNCH_CHECK("moe_decode_in: sum launch");
   return ok();
+} catch (...) {
+  return fail(BITSMOE_ERR_NOMEM, "moe_decode_in: host allocation failed");
 }
