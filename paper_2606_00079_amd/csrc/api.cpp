@@ -3,6 +3,7 @@
 #include <dlfcn.h>
 #include <hip/hip_runtime_api.h>
 
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -38,22 +39,22 @@ bitsmoe_status device_error(const char* what, int hip_err) {
 }
 
 int device_cus() {
-  static std::mutex mu;
-  static std::map<int, int> cache;
+  // (a fixed table: the decode that promises to allocate nothing comes here)
+  static std::atomic<int> cache[64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) {
     (void)hipGetLastError();
     return 256;
   }
-  std::lock_guard<std::mutex> lock(mu);
-  auto it = cache.find(dev);
-  if (it != cache.end()) return it->second;
+  const bool cached = dev >= 0 && dev < 64;
+  if (cached)
+    if (const int known = cache[dev].load(std::memory_order_relaxed)) return known;
   int n = 0;
   if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) {
     (void)hipGetLastError();
     n = 256;
   }
-  cache[dev] = n;
+  if (cached) cache[dev].store(n, std::memory_order_relaxed);
   return n;
 }
 

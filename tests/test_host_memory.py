@@ -42,3 +42,16 @@ def test_decode_routing_tables_without_memory(entry, B, nnz, more):
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr[-2000:]
     assert r.stdout.startswith("status 5 ") and "host allocation" in r.stdout, r.stdout
+
+
+def test_device_cus_allocates_nothing(tmp_path):
+    """The number of compute units is looked up once per device, on the path of
+    the decode that promises to allocate nothing (any device index works)."""
+    from paper_2606_00079_amd import build as b
+    exe = str(tmp_path / "device_cus_check")
+    subprocess.run(["g++", *b.CXX_FLAGS, f"-I{b.INCLUDE}", f"-I{b.CSRC}", "-o", exe,
+                    os.path.join(ROOT, "tests", "device_cus_check.cpp"), os.path.join(b.CSRC, "api.cpp"),
+                    f"-L{b.ROCM}/lib", f"-Wl,-rpath,{b.ROCM}/lib", "-lamdhip64", "-ldl"], check=True)
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=60, check=True).stdout.split()
+    assert out[:5] == ["100", "103", "103", "100", "170"]
+    assert out[5] == "3" and out[6] == "0", out
