@@ -247,7 +247,7 @@ bitsmoe_status bitsmoe_allocate(const float* L_host, int64_t units, const int* b
  *                  every unit whose reduced cost at the LP-relaxation
  *                  multiplier exceeds the LP gap (such a unit takes the same
  *                  width in every optimum) and run the exact program on the
- *                  rest.  < 0 selects the default (2^26).
+ *                  rest.  < 0 selects the default (0: fixing first at any size).
  *   core_units_out number of units left to the exact program (may be NULL).
  */
 bitsmoe_status bitsmoe_allocate_ex(const float* L_host, int64_t units, const int* bits_host,

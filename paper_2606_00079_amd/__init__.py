@@ -477,7 +477,7 @@ def allocate(L, bits: Sequence[int], budget: int, full_dp_limit: int = -1,
     _check(lib().bitsmoe_allocate_ex(Lh.ctypes.data_as(ctypes.c_void_p), units, bp, len(b),
                                      int(budget), out.ctypes.data_as(ctypes.c_void_p),
                                      ctypes.byref(obj), int(full_dp_limit),
-                                     ctypes.byref(core) if return_core else None),
+                                     ctypes.byref(core)),
            "allocate")
     if return_core:
         return out, obj.value, core.value

@@ -64,7 +64,7 @@ def test_allocate_matches_oracle_dp(lib, seed, force_core):
     for frac in (0.0, 0.3, 0.5, 0.77, 1.0):
         budget = int(U * bits[0] + frac * U * (bits[-1] - bits[0]))
         ref, _ = oracle.allocate_dp(L, bits, budget)
-        got, obj, core = pkg.allocate(L, bits, budget, full_dp_limit=0 if force_core else -1,
+        got, obj, core = pkg.allocate(L, bits, budget, full_dp_limit=0 if force_core else 1 << 40,
                                       return_core=True)
         assert np.array_equal(got, ref), (U, bits, budget)
         assert np.isclose(obj, oracle.objective(L, bits, ref), rtol=1e-12)
@@ -79,7 +79,7 @@ def test_allocate_matches_exhaustive_tiny(lib):
         L = _rand_L(g, U, 4, ties=True)
         budget = int(g.integers(U, 4 * U + 1))
         ref, _ = oracle.allocate_exhaustive(L, bits, budget)
-        for lim in (-1, 0):
+        for lim in (-1, 0, 1 << 40):
             got, _ = pkg.allocate(L, bits, budget, full_dp_limit=lim)
             assert np.array_equal(got, ref)
 
@@ -126,6 +126,15 @@ def test_allocate_order_of_equal_slopes(lib, kind):
             for kw in ({}, {"full_dp_limit": 0}):
                 got, obj = pkg.allocate(L, bits, budget, **kw)
                 assert np.array_equal(got, ref) and obj == ro, (U, budget)
+
+
+def test_allocate_core_size_is_that_of_the_default_method(lib):
+    """Asking for the size of the core does not change the method: the default
+    fixes first at any size."""
+    L = _rand_L(np.random.default_rng(3), 300, 4)
+    for lim, fixes in ((-1, True), (0, True), (1 << 40, False)):
+        _, _, core = pkg.allocate(L, [1, 2, 3, 4], 600, full_dp_limit=lim, return_core=True)
+        assert (core < 100) if fixes else (core == 300), (lim, core)
 
 
 @pytest.mark.parametrize("U", [341, 342, 1500])
@@ -236,7 +245,7 @@ def test_allocate_surrogate_widths_match_oracle(lib, seed, force_core):
     L = sg.surrogate_table(C.astype(np.float64), H, gamma=0.7).astype(np.float32)
     for budget in (0, 150, 2 * U, 5 * U):
         ref, _ = oracle.allocate_dp(L, sg.WIDTHS, budget)
-        got, _ = pkg.allocate(L, sg.WIDTHS, budget, full_dp_limit=0 if force_core else -1)
+        got, _ = pkg.allocate(L, sg.WIDTHS, budget, full_dp_limit=0 if force_core else 1 << 40)
         assert np.array_equal(got, ref), budget
         assert int(got.astype(np.int64).sum()) <= budget
 
