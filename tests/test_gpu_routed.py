@@ -196,6 +196,37 @@ def test_score_scale_of_matrices_without_a_dominant_diagonal(scale):
     assert np.array_equal(many, np.tile(L, (n, 1)))
 
 
+@pytest.mark.parametrize("nh,d", [(9, 1024), (1, 2112)])
+def test_score_scale_second_look_takes_several_blocks(nh, d):
+    """Matrices that fail the check of H_off's scale and have more blocks than
+    the second look has workgroups (80 against 32 for more than eight
+    matrices, 306 against 256 for one): every block is converted again.  The
+    entries are random, so that a block left at the first scale would be wrong
+    by a power of two in every row.  Bound as above."""
+    say("second look", nh, d)
+    g = np.random.default_rng(nh)
+    upe, bits, group = 64, (1, 2, 3, 4), 64
+    S = g.standard_normal((nh, d, d)).astype(np.float32)
+    S = (S + S.transpose(0, 2, 1)) / 2
+    for e in range(nh):  # in a block of its own for every matrix
+        i, k = (29 * e) % d, d - 1 - (97 * e) % d
+        S[e, i, k] = S[e, k, i] = 300.0
+    C = synth.random_rows(nh * upe, d, seed=d, scale=0.05, heavy=True)
+    L = bm.score_routed(dev(C, "f32"), dev(S, "f32"), upe, bits, group).cpu().numpy()
+    for e in range(nh):
+        rows = C[e * upe:(e + 1) * upe]
+        H64 = S[e].astype(np.float64)
+        ref = oracle.score(rows, H64, bits, group)
+        den = np.maximum(np.abs(oracle.score(rows, np.abs(H64), bits, group)),
+                         np.linalg.norm(H64) * _err2(rows, bits, group))
+        err = np.abs(L[e * upe:(e + 1) * upe] - ref)
+        assert np.all(err <= 2.0**-10 * den), (e, float(np.max(err / den)))
+        if nh > 1:  # alone it takes the pass over all entries: the same bits (an even
+            # number of row tiles: every sum runs in the same order)
+            one = bm.score(dev(rows, "f32"), dev(S[e], "f32"), bits, group).cpu().numpy()
+            assert np.array_equal(one, L[e * upe:(e + 1) * upe])
+
+
 def _err2(rows, bits, group):
     """|delta|^2 of every row and width: the loss under H = I."""
     return oracle.score(rows, np.eye(rows.shape[1]), bits, group)
