@@ -619,18 +619,19 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu_polls(const double* M_dev, in
   hipStream_t s = static_cast<hipStream_t>(stream);
   bitsmoe_status st;
   // work matrix (M, then the reflectors by rows), Z^T, and small buffers:
-  // Wp [NB][n], trsymv output [n + 2 NB], d, e, tau, v [n], G and T [NB][NB],
-  // X [r][NB], the in-register reduction's exchange, and what the host reads:
+  // Wp [NB][n], trsymv output [n + 2 NB], d, e, tau, v [n], G and T (the panels'
+  // compact forms, of either width), X [r][NB], the in-register reduction's exchange, and what the host reads:
   // eigenvalues [r], info [8], the reduction's error flag, a flag per vector [r]
   double* A = static_cast<double*>(scratch(kScratchA, static_cast<size_t>(n * n) * 8, stream, &st));
   if (!A) return st;
   double* Zt = static_cast<double*>(scratch(kScratchB, static_cast<size_t>(r * n) * 8, stream, &st));
   if (!Zt) return st;
   const int64_t npan = (n - 1 + NB - 1) / NB;
+  const int64_t g_words = std::max<int64_t>(npan, 1) * NB * NB;
+  const int64_t t_words = std::max(g_words, static_cast<int64_t>(backtransform_bytes(n) / 8));
   const size_t ex_words = tridiag_resident_bytes(n) / 8;
   const size_t res_words = static_cast<size_t>(r + 9 + (r + 7) / 8);
-  const size_t small = (static_cast<size_t>(NB * n + (n + 2 * NB) + 4 * n +
-                                            2 * std::max<int64_t>(npan, 1) * NB * NB + r * NB) +
+  const size_t small = (static_cast<size_t>(NB * n + (n + 2 * NB) + 4 * n + g_words + t_words + r * NB) +
                         ex_words + res_words) * 8;
   double* Wp = static_cast<double*>(scratch(kScratchPart, small, stream, &st));
   if (!Wp) return st;
@@ -639,9 +640,9 @@ extern "C" bitsmoe_status bitsmoe_shared_basis_gpu_polls(const double* M_dev, in
   double* evec = dvec + n;
   double* tau = evec + n;
   double* vbuf = tau + n;  // the current column's reflector
-  double* G = vbuf + n;                                 // [npan][NB][NB]
-  double* T = G + std::max<int64_t>(npan, 1) * NB * NB;  // [npan][NB][NB]
-  double* X = T + std::max<int64_t>(npan, 1) * NB * NB;
+  double* G = vbuf + n;     // [npan][NB][NB]
+  double* T = G + g_words;  // [npan][NB][NB], or the register form's
+  double* X = T + t_words;
   double* exch = X + r * NB;
   double* wd = exch + ex_words;  // eigenvalues
   double* info = wd + r;
