@@ -1197,6 +1197,112 @@ __global__ __launch_bounds__(256) void yin_kernel(
   }
 }
 
+// The same for jobs of four tokens in large batches: 32 outputs a thread (a
+// word of each plane), one row at a time, nothing staged.  There are waves
+// enough to cover a row's chain of loads then, and what counts is how many sums
+// a thread does per row that it loads and decodes: 128 here against 64, both at three
+// waves per SIMD.  With both in one form (32 outputs and staged rows) the planes
+// of a row held at once take 287 registers, one wave per SIMD, twice the time.
+// 512 tokens of 8 experts of 384 x 7168: 581 us in all, against 801 for yin_kernel.
+__global__ __launch_bounds__(256) void yin_wide_kernel(
+    const uint32_t* __restrict__ codes32, const uint32_t* __restrict__ params,
+    const uint8_t* __restrict__ bits, const int64_t* __restrict__ off, int64_t total_words,
+    int r, int d, int gshift, int SEGW, int rows_split, const float* __restrict__ z,
+    const int4* __restrict__ jobs, const float* __restrict__ ew, int64_t nnz,
+    float* __restrict__ yp) {
+  constexpr int T = 4, kPad = kSeg + 1;
+  __shared__ float red[256 * kPad];
+  const int4 job = jobs[2 * blockIdx.y];
+  const int4 jt = jobs[2 * blockIdx.y + 1];
+  const int e = job.x;
+  const int64_t i0 = job.y;
+  const int tk[T] = {jt.x, jt.y, jt.z, jt.w};
+  const int RSL = 256 / SEGW;
+  const int rs = static_cast<int>(threadIdx.x) / SEGW, sg_local = static_cast<int>(threadIdx.x) - rs * SEGW;
+  const int nseg = d / kSeg;
+  const int sg = static_cast<int>(blockIdx.x) * SEGW + sg_local;
+  const int64_t nw = d / 64;
+  const int kb = static_cast<int>(blockIdx.z) * rows_split;
+  const int ke = min(r, kb + rows_split);
+  float acc[T][kSeg];
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int j = 0; j < kSeg; ++j) acc[t][j] = 0.0f;
+  if (rs < RSL && sg < nseg) {
+    for (int k = kb + rs; k < ke; k += RSL) {
+      const int64_t u = static_cast<int64_t>(e) * r + k;
+      const int b = bits[u];
+      const int64_t o0 = off[u], o1 = off[u + 1];
+      // a unit whose width or offsets are inconsistent contributes nothing
+      if (!(width_ok(b) && b != 0 && o1 - o0 == b * nw && o0 >= 0 && o1 <= total_words)) continue;
+      float zk[T];
+#pragma unroll
+      for (int t = 0; t < T; ++t) zk[t] = t < job.z ? z[static_cast<int64_t>(tk[t]) * r + k] : 0.0f;
+      if (b == 16) {
+        const uint2* h = reinterpret_cast<const uint2*>(codes32 + 2 * o0) + (kSeg / 4) * sg;
+#pragma unroll
+        for (int q = 0; q < kSeg / 4; ++q) {
+          const uint2 v = h[q];
+          const float c[4] = {f16_bits_to_f32(static_cast<uint16_t>(v.x & 0xffffu)),
+                              f16_bits_to_f32(static_cast<uint16_t>(v.x >> 16)),
+                              f16_bits_to_f32(static_cast<uint16_t>(v.y & 0xffffu)),
+                              f16_bits_to_f32(static_cast<uint16_t>(v.y >> 16))};
+#pragma unroll
+          for (int c4 = 0; c4 < 4; ++c4)
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t][4 * q + c4] = fmaf(zk[t], c[c4], acc[t][4 * q + c4]);
+        }
+        continue;
+      }
+      const uint32_t prm = params[(u * d + sg * kSeg) >> gshift];
+      const float s = f16_bits_to_f32(static_cast<uint16_t>(prm & 0xffffu));
+      const float m = f16_bits_to_f32(static_cast<uint16_t>(prm >> 16));
+      const uint32_t* pw = codes32 + 2 * o0 + sg;  // plane t: word 2 (o0 + t nw) + sg
+      uint32_t qb[kSeg / 4];
+      {
+        const uint32_t p0 = pw[0];
+#pragma unroll
+        for (int kk = 0; kk < kSeg / 4; ++kk) qb[kk] = spread4(p0 >> (4 * kk));
+      }
+      for (int t = 1; t < b; ++t) {
+        const uint32_t pt = pw[2 * t * nw];
+#pragma unroll
+        for (int kk = 0; kk < kSeg / 4; ++kk) qb[kk] |= spread4(pt >> (4 * kk)) << t;
+      }
+#pragma unroll
+      for (int kk = 0; kk < kSeg / 4; ++kk)
+#pragma unroll
+        for (int c4 = 0; c4 < 4; ++c4) {
+          const float cv = fmaf(static_cast<float>((qb[kk] >> (8 * c4)) & 0xffu), s, m);
+#pragma unroll
+          for (int t = 0; t < T; ++t) acc[t][4 * kk + c4] = fmaf(zk[t], cv, acc[t][4 * kk + c4]);
+        }
+    }
+  }
+  // slices in order, one token at a time: red[rs][sg_local][j]
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    if (t >= job.z) continue;  // uniform over the workgroup
+    __syncthreads();
+    if (rs < RSL) {
+#pragma unroll
+      for (int j = 0; j < kSeg; ++j) red[(rs * SEGW + sg_local) * kPad + j] = acc[t][j];
+    }
+    __syncthreads();
+    const float wt = ew[i0 + t];
+    for (int idx = threadIdx.x; idx < SEGW * kSeg; idx += 256) {
+      const int sgl = idx / kSeg, j = idx - sgl * kSeg;
+      const int sgo = static_cast<int>(blockIdx.x) * SEGW + sgl;
+      if (sgo >= nseg) continue;
+      float v = 0.0f;
+      for (int q = 0; q < RSL; ++q) v += red[(q * SEGW + sgl) * kPad + j];
+      yp[(static_cast<int64_t>(blockIdx.z) * nnz + i0 + t) * d + static_cast<int64_t>(sgo) * kSeg + j] =
+          wt * v;
+    }
+  }
+}
+
 // y[b][o] = the sum of the partials yp[rz][i][o] over the row splits rz and
 // token b's routing entries i: P = nsplit kmax partials per output.  A
 // workgroup covers 64 outputs of one token; token b's entry list is staged
@@ -1805,13 +1911,20 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
   const int tmax = nnz <= 2 * busy && (nnz + busy) / 2 <= 65535 ? 2 : 4;
   st = build_routing("moe_decode_in", E, B, offsets_host, tokens_host, weights_host, tmax, &rt);
   if (st != BITSMOE_OK) return st;
-  // segments of 16 outputs: SEGW per workgroup (up to 256), RSL = 256 / SEGW
+  // Jobs of four take yin_wide_kernel from 1e8 entries decoded in all: below,
+  // yin_kernel's smaller pieces fill the device better (24 jobs of 384 x 7168, 6.6e7:
+  // 109 us against 119; 13 of 1000 x 14336, jobs of two in fact: 121 against
+  // 158), above it is bound by its instructions (32 of 384 x 7168, 8.8e7:
+  // 143 against 125; 96, 2.6e8: 291 against 250; 215 of 384 x 1408, 1.2e8: 169
+  // against 132; 20 of 1000 x 14336, 2.9e8: 235 against 202).
+  const bool wide = rt.T == 4 && static_cast<double>(rt.njobs) * static_cast<double>(r * d_out) >= 1e8;
+  // segments of 16 (32) outputs: SEGW per workgroup (up to 256), RSL = 256 / SEGW
   // row slices; rows split over blockIdx.z for about 1024 workgroups but at
   // least four rows per thread and 32 in all (each split adds a partial per
   // output to the final sum: at 23 tokens of a 384 x 768 projection half as many
   // splits moved 3 us from the sum to the rows, at one token 20 splits of 20
   // rows took 41.9 us where 12 of 32 take 40.5)
-  const int64_t nseg = d_out / kInSeg;
+  const int64_t nseg = d_out / (wide ? kSeg : kInSeg);
   const int SEGW = static_cast<int>(std::min<int64_t>(nseg, 256));
   const int RSL = 256 / SEGW;
   const int64_t segblocks = (nseg + SEGW - 1) / SEGW;
@@ -1852,11 +1965,18 @@ extern "C" bitsmoe_status bitsmoe_moe_decode_in(const uint64_t* codes_dev, const
     KernelTimer timer("moe_decode_in_y", stream);
     dim3 grid(static_cast<unsigned>(segblocks), static_cast<unsigned>(rt.njobs),
               static_cast<unsigned>(nsplit));
-#define BITSMOE_DECIN(TT)                                                                           \
-  hipLaunchKernelGGL(yin_kernel<TT>, grid, dim3(256), 0, s, c32, pr, bits_dev, word_offsets_dev,    \
+#define BITSMOE_DECIN(KERNEL)                                                                       \
+  hipLaunchKernelGGL(KERNEL, grid, dim3(256), 0, s, c32, pr, bits_dev, word_offsets_dev,    \
                      total_words, static_cast<int>(r), static_cast<int>(d_out), __builtin_ctz(group), SEGW, \
                      static_cast<int>(rows_split), z, up.jobs, up.w, rt.nnz, yp)
-    if (rt.T == 4) BITSMOE_DECIN(4); else if (rt.T == 2) BITSMOE_DECIN(2); else BITSMOE_DECIN(1);
+    if (wide)
+      BITSMOE_DECIN(yin_wide_kernel);
+    else if (rt.T == 4)
+      BITSMOE_DECIN(yin_kernel<4>);
+    else if (rt.T == 2)
+      BITSMOE_DECIN(yin_kernel<2>);
+    else
+      BITSMOE_DECIN(yin_kernel<1>);
 #undef BITSMOE_DECIN
   }
   BITSMOE_LAUNCH_CHECK("moe_decode_in: y launch");

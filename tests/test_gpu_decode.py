@@ -242,6 +242,20 @@ def test_moe_decode_in_edges(E, r, d_out, d_in, B, k, G, widths):
     assert relfro(Y, ref) <= REL
 
 
+@pytest.mark.parametrize("E,r,d_out,d_in,B,k,G,widths", [
+    (2, 601, 4160, 640, 85, 2, 64, (0, 1, 2, 3, 5, 8, 16)),  # last job of one, 130 of 256 threads, 19 splits
+    (3, 1990, 64, 2000, 1601, 2, 32, (1, 2, 4, 16)),         # two segments, 128 row slices
+    (2, 200, 9216, 256, 113, 2, 256, (2, 6, 7)),             # two segment blocks, the second nearly empty
+    (2, 200, 9216, 256, 104, 2, 256, (2, 6, 7)),             # just below the line: the other kernel
+])
+def test_moe_decode_in_large_batches(E, r, d_out, d_in, B, k, G, widths):
+    """Jobs of four around 1e8 decoded entries, where the row kernel with 32
+    outputs a thread takes over."""
+    say("decode_in large", E, r, d_out, d_in, B, k, G, widths)
+    Y, ref = _run_in(E, r, d_out, d_in, B, k, G, widths, seed=E + r + B)
+    assert relfro(Y, ref) <= 2e-6  # fp32 sums
+
+
 def test_moe_decode_in_many_experts():
     """65535 experts, every other one with three entries and the others with
     one: two entries per expert on average, but 98302 jobs of up to two (the
