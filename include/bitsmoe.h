@@ -124,9 +124,9 @@ bitsmoe_status bitsmoe_gram(const void* X_dev, bitsmoe_dtype xt, int64_t n, int6
  * Step 1b -- cross-expert Gram.
  * M = sum_e W_e W_e^T = W_cat W_cat^T, whose eigenvectors are the left
  * singular vectors of W_cat = [W_1 ... W_E] (App. B.1, Eqs. app_down_w_cat,
- * app_down_cat_svd_absorbed).  Partial sums over K chunks of at most 4096
- * terms are formed in fp32 and added in fp64 in a fixed order, so the result
- * is deterministic.
+ * app_down_cat_svd_absorbed).  Where the output's tiles alone leave compute units
+ * idle the E * d_in terms are split over several workgroups, whose fp32 sums
+ * are added in fp64 in a fixed order; the result is deterministic.
  *   W_dev  [E][d_out][d_in] of type wt
  *   M_dev  [d_out][d_out] fp64 output, full symmetric.
  * Shape rules: E >= 1, d_out % 64 == 0, d_in % 64 == 0.
@@ -157,22 +157,26 @@ bitsmoe_status bitsmoe_shared_basis(const double* M_dev, int64_t d_out, int64_t 
  * Step 2 on the GPU: the same outputs and conventions as
  * bitsmoe_shared_basis (eigenvalues descending, each eigenvector's entry of
  * largest magnitude positive), computed on the device:
- *   1. a blocked Householder reduction of M to tridiagonal form Q^T M Q
- *      (fp64, panels of 32 columns);
- *   2. eigenvalues d_out-r+1..d_out of the tridiagonal matrix by bisection,
- *      eigenvectors by inverse iteration (tridiagonal LU with partial
- *      pivoting), eigenvectors of eigenvalues closer than 1e-7 ||T|| made
- *      orthonormal by modified Gram-Schmidt;
+ *   1. a Householder reduction of M to tridiagonal form Q^T M Q (fp64): up
+ *      to d_out = 2048 in one launch with M in registers (of one workgroup up
+ *      to 128, of eight rows per compute unit above), beyond in panels of 32
+ *      columns.  Should the workgroups of the one launch not come to run
+ *      together (a device kept busy for seconds), the panels take over;
+ *   2. eigenvalues d_out-r+1..d_out of the tridiagonal matrix by multisection
+ *      on Sturm counts, eigenvectors by twisted factorizations; those of
+ *      eigenvalues closer than 1e-7 ||T|| by inverse iteration (tridiagonal LU
+ *      with partial pivoting) and made orthonormal by modified Gram-Schmidt;
  *   3. the back-transformation U = Q Z.
- * Only the two diagonals (for bounds and the finiteness check) and the r
- * eigenvalues cross PCIe.  Inside clusters of (nearly) equal eigenvalues
- * the eigenvectors are a valid orthonormal basis of the cluster but need not
- * equal bitsmoe_shared_basis's.
+ * Only the r eigenvalues and a few flags cross PCIe.  Inside clusters of
+ * (nearly) equal eigenvalues the eigenvectors are a valid orthonormal basis of
+ * the cluster but need not equal bitsmoe_shared_basis's; for M = 0 they are
+ * unit vectors.
  *   Arguments as bitsmoe_shared_basis; host_ms is the wall time of the
  *   whole call.
- * Shape rules: 1 <= r <= d_out <= 65536.  Device scratch: (d_out + 6 r)
- * d_out doubles.  The call waits for the stream.  A non-finite M gives
- * BITSMOE_ERR_NUMERIC.
+ * Shape rules: 1 <= r <= d_out <= 65536.  Device scratch: about (d_out + r)
+ * d_out doubles, 2 r d_out more above d_out = 3584, and up to 5 r d_out in their
+ * place where eigenvalues are in clusters.  The call waits for the stream.  A
+ * non-finite M gives BITSMOE_ERR_NUMERIC.
  */
 bitsmoe_status bitsmoe_shared_basis_gpu(const double* M_dev, int64_t d_out, int64_t r,
                                         float* Ut_dev, double* eigvals_host, double* host_ms,
@@ -319,8 +323,8 @@ bitsmoe_status bitsmoe_score_diag(const float* C_dev, int64_t units, int64_t d,
  * with the same 1/n as bitsmoe_gram (so, with every token's weights summing
  * to 1, sum_e H_e is the shared Gram).  The routed rows are gathered on the
  * device (the weighted side split into bf16 hi + lo) and all experts' Grams
- * run in one batched symmetric matrix-core launch, reduced in fp64 in a
- * fixed order.
+ * run in one batched symmetric matrix-core launch (split over K as
+ * bitsmoe_gram_experts where there are few; deterministic).
  *   X_dev         [n][d] of type xt (calibration rows)
  *   offsets_host  [E + 1] non-decreasing, offsets[0] = 0 (host)
  *   rows_host     [offsets[E]] row of X of each routed entry, in [0, n) (host)
